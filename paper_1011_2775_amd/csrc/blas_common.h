@@ -12,7 +12,6 @@ namespace wcmg {
 namespace blas_detail {
 
 constexpr int kThreads = 256;
-constexpr int kMaxK = 16;
 
 template <typename T>
 struct C2;
@@ -39,36 +38,23 @@ __device__ __forceinline__ void st(void* p, size_t i, cpx<double> c) {
   reinterpret_cast<V*>(p)[i] = v;
 }
 
-// Reduce NR doubles over the block into partial[blockIdx.x*NR + k].
-template <int NR>
-__device__ __forceinline__ void block_reduce_to(double (&v)[NR], double* partial) {
-  __shared__ double sh[NR][kThreads / 64];
-#pragma unroll
-  for (int k = 0; k < NR; ++k) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NR; ++k) sh[k][wave] = v[k];
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < NR) {
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) s += sh[threadIdx.x][w];
-    partial[(size_t)blockIdx.x * NR + threadIdx.x] = s;
-  }
-}
-// Grid-wide sum of NR doubles in one launch: every block stores its partials
-// (device-coherent), counts itself in o.counter, and the last block to
+// Sum of NR doubles over nb blocks in one launch: every block stores its
+// partials (device-coherent), counts itself in *counter, and the last block to
 // arrive adds the partials in block order (TPV threads per value over fixed
 // strided subsets of the blocks, then a fixed shuffle tree) and writes the
-// first nvalid sums to o.res (and o.hres); it then rearms the counter.  The
+// first nvalid sums to res (and hres); it then rearms the counter.  The
 // order of the additions never depends on which block finishes last.
+// block: this block's place 0 .. nb-1 in the sum; partial: nb x NR doubles.
+// Several sums share a launch (one per right-hand side or group of vectors)
+// when each has partials and a row of counters of its own.
+//
+// Atomic adds to one cache line take turns (about 10 ns each), so a row holds
+// eight counters on lines of their own, each counting every eighth block, and
+// one that counts the eight: 4608 adds to one line had cost k_cdot_norm_b with
+// twelve right-hand sides 45 of its 70 us.
 template <int NR>
-__device__ __forceinline__ void block_reduce(double (&v)[NR], const RedOut& o, int nvalid = NR) {
+__device__ __forceinline__ void block_reduce_row(double (&v)[NR], double* partial, unsigned* counter, int nb,
+                                                 int block, double* res, double* hres, int nvalid) {
   __shared__ double sh[NR][kThreads / 64];
   __shared__ double shw[kThreads / 64];
   __shared__ int last_s;
@@ -87,17 +73,23 @@ __device__ __forceinline__ void block_reduce(double (&v)[NR], const RedOut& o, i
     double s = 0.0;
 #pragma unroll
     for (int w = 0; w < kThreads / 64; ++w) s += sh[threadIdx.x][w];
-    __hip_atomic_store(o.partial + (size_t)blockIdx.x * NR + threadIdx.x, s, __ATOMIC_RELAXED,
+    __hip_atomic_store(partial + (size_t)block * NR + threadIdx.x, s, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   }
   // the partial stores are complete (and coherent) before the block counts itself
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0)
-    last_s = __hip_atomic_fetch_add(o.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  if (threadIdx.x == 0) {
+    const int sub = block & 7;
+    const unsigned mine = (nb - sub + 7) >> 3, subs = nb < 8 ? nb : 8;
+    bool last = __hip_atomic_fetch_add(counter + (sub + 1) * kCounterLine, 1u, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT) == mine - 1;
+    if (last)
+      last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == subs - 1;
+    last_s = last;
+  }
   __syncthreads();
   if (!last_s) return;
-  const int nb = gridDim.x;
   int tpv = 1;
   while (tpv * 2 * nvalid <= kThreads && tpv < nb) tpv *= 2;
   const int t = threadIdx.x, vv = t / tpv, j = t - vv * tpv;
@@ -109,13 +101,13 @@ __device__ __forceinline__ void block_reduce(double (&v)[NR], const RedOut& o, i
       double p[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        p[u] = __hip_atomic_load(o.partial + (size_t)(b + u * tpv) * NR + vv, __ATOMIC_RELAXED,
+        p[u] = __hip_atomic_load(partial + (size_t)(b + u * tpv) * NR + vv, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += p[u];
     }
     for (; b < nb; b += tpv)
-      s += __hip_atomic_load(o.partial + (size_t)b * NR + vv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s += __hip_atomic_load(partial + (size_t)b * NR + vv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   const int width = tpv < 64 ? tpv : 64;
   for (int off = width >> 1; off > 0; off >>= 1) s += __shfl_down(s, off, width);
@@ -129,10 +121,15 @@ __device__ __forceinline__ void block_reduce(double (&v)[NR], const RedOut& o, i
     }
   }
   if (j == 0 && vv < nvalid) {
-    o.res[vv] = s;
-    if (o.hres) o.hres[vv] = s;
+    res[vv] = s;
+    if (hres) hres[vv] = s;
   }
-  if (threadIdx.x == 0) __hip_atomic_store(o.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x < 9)
+    __hip_atomic_store(counter + threadIdx.x * kCounterLine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <int NR>
+__device__ __forceinline__ void block_reduce(double (&v)[NR], const RedOut& o) {
+  block_reduce_row<NR>(v, o.partial, o.counter, gridDim.x, blockIdx.x, o.res, o.hres, NR);
 }
 
 // enough blocks that every thread handles about 8 elements, at most

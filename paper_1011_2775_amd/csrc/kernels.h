@@ -90,14 +90,18 @@ void clover_relayout(int prec, void* dst, const double* src, int Vh, hipStream_t
 // ------------------------------------------------------------ BLAS-1
 // Flat complex vectors of n elements, storage double (prec F64) or float (F32).
 // Reductions accumulate in double and are deterministic (grid fixed by n,
-// per-block partials summed in block order by a one-block second pass).
+// per-block partials summed in block order by the last block to arrive).
 constexpr int kRedBlocks = 512;
+constexpr int kRedPartials = kRedBlocks * 128;
+// arrival counters of a sum: nine, a cache line apart, padded to a row; kRedRows sums at once
+constexpr int kCounterLine = 32;
+constexpr int kCounterRow = 16 * kCounterLine;
+constexpr int kRedRows = 160;
 struct RedOut {
   double* res;        // device result
-  double* partial;    // kRedBlocks * 32 doubles of per-block partials
-  unsigned* counter;  // arrival counter of the in-launch finish (zero between launches)
+  double* partial;    // kRedPartials doubles of per-block partials
+  unsigned* counter;  // rows of arrival counters of the in-launch finish (zero between launches)
   double* hres;       // optional second destination of the result (nullptr: none)
-  RedOut at(int off) const { return RedOut{res + off, partial, counter, hres ? hres + off : nullptr}; }
 };
 void blas_zero(int prec, void* x, size_t n, hipStream_t st);
 // y (storage prec_dst) = x (storage prec_src), n complex elements
@@ -112,11 +116,14 @@ void blas_norm2(int prec, const void* x, size_t n, const RedOut& o, hipStream_t 
 void blas_cdot(int prec, const void* x, const void* y, size_t n, const RedOut& o, hipStream_t st);
 // res[0..1] = <x,y>, res[2] = ||x||^2
 void blas_cdot_norm(int prec, const void* x, const void* y, size_t n, const RedOut& o, hipStream_t st);
-// res[2j..2j+1] = <v_j, y> for j < k (writes up to 2*(k rounded up to 16) slots)
+// res[2j..2j+1] = <v_j, y> for j < k
 void blas_multi_cdot(int prec, const void* const* v, int k, const void* y, size_t n, const RedOut& o,
                      hipStream_t st);
 // y += sum_j c_j v_j  (c on host)
 void blas_multi_axpy(int prec, const double* c, const void* const* v, int k, void* y, size_t n, hipStream_t st);
+// the same with c in device memory
+void blas_multi_axpy_dev(int prec, const double* coef, const void* const* v, int k, void* y, size_t n,
+                         hipStream_t st);
 // y += a x ; res[0] = ||y||^2
 void blas_axpy_norm(int prec, double ar, double ai, const void* x, void* y, size_t n, const RedOut& o,
                     hipStream_t st);
@@ -131,19 +138,14 @@ void blas_mr_update(int prec, double ar, double ai, void* x, void* r, const void
 
 // Device-resident GCR coefficients: slot j of qa holds {||q_j||^2, <q_j,r>, ||r||^2
 // after step j}; beta holds the multi-dot <q_j, y>.  No host round trip.
-// x += sum_j alpha_j z_j
-// qa[4j..4j+3] = {1, dots[2j], dots[2j+1], 0} for j < K (coefficients x += sum_j dots_j z_j
-// for blas_gcr_update_x_dev)
-void blas_defl_coefs(const double* dots, double* qa, int K, hipStream_t st);
-void blas_gcr_update_x_dev(int prec, const void* const* z, int k, void* x, size_t n, const double* qa,
-                           hipStream_t st);
 // One step of the GCR kept with raw preconditioned directions, after
 // blas_multi_cdot of y against {q_0 .. q_{k-1}, y, r} into beta: y -= sum_j
 // (beta_j/||q_j||^2) q_j; ||y||^2 by the Pythagorean sum and <y, r> (r is
-// orthogonal to every q_j) into qa[4k], qa[4k+1..2]; r -= alpha y; ||r||^2
-// into o; the coefficients beta_j/||q_j||^2 into cj[0 .. 2k)
-void blas_gcr_step_dev(int prec, const void* const* q, int k, void* y, void* r, size_t n, const double* beta,
-                       double* qa, double* cj, const RedOut& o, hipStream_t st);
+// orthogonal to every q_j) into qa[4k], qa[4k+1..2]; rout = rin - alpha y (the
+// same vector or another); ||rout||^2 into o; the coefficients
+// beta_j/||q_j||^2 into cj[0 .. 2k)
+void blas_gcr_step_dev(int prec, const void* const* q, int k, void* y, const void* rin, void* rout, size_t n,
+                       const double* beta, double* qa, double* cj, const RedOut& o, hipStream_t st);
 // x += sum_j alpha_j z~_j for a cycle of kt slots (nf fixed ones first) kept as
 // raw z_j: z~_j = z_j - sum_{i<j} c_ij z~_i with c_ij = cmat[2 (j ldc + i) ..];
 // y (2 kt doubles of device scratch) receives the coefficients on the raw z_j
@@ -160,6 +162,7 @@ struct RedB {
   double* res;
   size_t rs;
   double* part;
+  unsigned* counter;
 };
 void blas_norm2_b(int prec, const void* x, size_t vs, size_t n, int nrhs, const RedB& o, hipStream_t st);
 void blas_cdot_norm_b(int prec, const void* x, const void* y, size_t vs, size_t n, int nrhs, const RedB& o,
@@ -168,8 +171,8 @@ void blas_multi_cdot_b(int prec, const void* const* v, int k, const void* y, siz
                        const RedB& o, hipStream_t st);
 // blas_gcr_step_dev / blas_gcr_update_x_raw for every right-hand side (rows of
 // beta, qa, cj / cmat and y bs, qs, cjs / cms and ys doubles apart)
-void blas_gcr_step_b(int prec, const void* const* q, int k, void* y, void* r, size_t vs, size_t n, int nrhs,
-                     const double* beta, size_t bs, double* qa, size_t qs, double* cj, size_t cjs, const RedB& o,
+void blas_gcr_step_b(int prec, const void* const* q, int k, void* y, const void* rin, void* rout, size_t vs, size_t n,
+                     int nrhs, const double* beta, size_t bs, double* qa, size_t qs, double* cj, size_t cjs, const RedB& o,
                      hipStream_t st);
 void blas_gcr_update_x_raw_b(int prec, const void* const* z, int kt, void* x, size_t vs, size_t n, int nrhs,
                              const double* qa, size_t qs, const double* cmat, size_t cms, int ldc, double* y,

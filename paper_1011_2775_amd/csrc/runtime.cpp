@@ -122,10 +122,10 @@ KernelTimer::~KernelTimer() {
 // ------------------------------------------------------------------ reducer
 void Reducer::init(hipStream_t s) {
   st = s;
-  partial.alloc((size_t)kRedBlocks * 64 * sizeof(double));
+  partial.alloc((size_t)kRedPartials * sizeof(double));
   res.alloc(256 * sizeof(double));
-  counter.alloc(256);
-  HIPCHK(hipMemset(counter.p, 0, 256));
+  counter.alloc((size_t)kRedRows * kCounterRow * sizeof(unsigned));
+  HIPCHK(hipMemset(counter.p, 0, (size_t)kRedRows * kCounterRow * sizeof(unsigned)));
   HIPCHK(hipHostMalloc((void**)&host, 256 * sizeof(double), hipHostMallocDefault));
   HIPCHK(hipHostMalloc((void**)&host2, 16 * sizeof(double), hipHostMallocDefault));
   for (auto& e : ev2) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));

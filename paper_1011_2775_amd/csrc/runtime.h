@@ -68,7 +68,7 @@ struct Reducer {
   hipEvent_t ev2[2] = {nullptr, nullptr};
   void fetch_async(const double* dev, int n, int slot);
   const double* fetch_wait(int slot);
-  RedB outb(double* dst, size_t rs) { return RedB{dst, rs, part_b.as<double>()}; }
+  RedB outb(double* dst, size_t rs) { return RedB{dst, rs, part_b.as<double>(), counter.as<unsigned>()}; }
   ~Reducer();
 };
 

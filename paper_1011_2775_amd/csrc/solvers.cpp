@@ -91,22 +91,26 @@ KrylovResult gcr(Ctx& c, GcrSpace& S, const OpFn& A, const OpFn* K, void* x, con
   // one step of the cycle: z_k = K r, q_k = A z_k, then <q_j, q> for the
   // basis, <q, q> and <r, q> in one pass and one pass that orthogonalises q
   // and updates r
+  // Without a preconditioner z_k is the residual itself: step k leaves the
+  // residual in the slot of z_k+1 and nothing is copied.
   auto enqueue_step = [&](int k) {
     void* z = S.Z[k].p;
     void* q = S.Q[k].p;
     const int kk = nf + k;  // basis slot of this step
     Qp[kk] = q;
     Zp[kk] = z;
+    const void* rin = K ? r : z;
+    void* rout = K || k + 1 == restart ? r : S.Z[k + 1].p;
     if (K)
       (*K)(z, r);
-    else
+    else if (k == 0)
       blas_copy(prec, z, r, n, st);
     A(q, z);
     for (int j = 0; j < kk; ++j) Dp[j] = Qp[j];
     Dp[kk] = q;
-    Dp[kk + 1] = r;
+    Dp[kk + 1] = rin;
     blas_multi_cdot(prec, Dp.data(), kk + 2, q, n, R.out(beta), st);
-    blas_gcr_step_dev(prec, Qp.data(), kk, q, r, n, beta, qa, cmat + (size_t)2 * kMaxRestart * kk,
+    blas_gcr_step_dev(prec, Qp.data(), kk, q, rin, rout, n, beta, qa, cmat + (size_t)2 * kMaxRestart * kk,
                       R.out(qa + 4 * kk + 3), st);
   };
   // The top-level solve reads each step's scalars back asynchronously and,
@@ -279,17 +283,20 @@ std::vector<KrylovResult> gcr_b(Ctx& c, GcrSpaceB& S, const OpFn& A, const OpFn*
         void* q = S.Q[k].p;
         Qp[k] = q;
         Zp[k] = z;
+        // as in gcr(): without a preconditioner the residual lives in the slots of z
+        const void* rin = K ? r : z;
+        void* rout = K || k + 1 == restart ? r : S.Z[k + 1].p;
         if (K)
           (*K)(z, r);
-        else
+        else if (k == 0)
           each([&](int, size_t o) { blas_copy(prec, (char*)z + o, (const char*)r + o, n, st); });
         A(q, z);
         for (int j = 0; j < k; ++j) Dp[j] = Qp[j];
         Dp[k] = q;
-        Dp[k + 1] = r;
+        Dp[k + 1] = rin;
         blas_multi_cdot_b(prec, Dp.data(), k + 2, q, vs, n, nr, R.outb(beta, cs), st);
-        blas_gcr_step_b(prec, Qp.data(), k, q, r, vs, n, nr, beta, cs, qa, cs, cmb + (size_t)2 * kMaxRestart * k, cms,
-                        R.outb(qa + 4 * k + 3, cs), st);
+        blas_gcr_step_b(prec, Qp.data(), k, q, rin, rout, vs, n, nr, beta, cs, qa, cs,
+                        cmb + (size_t)2 * kMaxRestart * k, cms, R.outb(qa + 4 * k + 3, cs), st);
         ++k;
         ++iters;
         if (fixed) {
@@ -956,11 +963,9 @@ struct MGSolver {
     }
     D.qa = L.defl_qa.as<double>();
     double* dots = L.defl_tmp.as<double>();
-    double* coef = dots + 2 * (kMaxRestart + 16);
     blas_multi_cdot(WCMG_F64, D.Q.data(), L.defl_k, rhs, n, c.red.out(dots), st);
-    blas_defl_coefs(dots, coef, L.defl_k, st);
     blas_zero(WCMG_F64, V.d_y.p, n, st);
-    blas_gcr_update_x_dev(WCMG_F64, D.Z.data(), L.defl_k, V.d_y.p, n, coef, st);
+    blas_multi_axpy_dev(WCMG_F64, dots, D.Z.data(), L.defl_k, V.d_y.p, n, st);
     const bool fx = fixed();
     const double bn = fx ? 1.0 : std::sqrt(norm2(c, WCMG_F64, rhs, n));
     OpFn A = [&](void* o, const void* i) {
