@@ -34,6 +34,9 @@ def hipcc():
 def flags():
     return ["-x", "hip", "--offload-arch=" + ARCH, "-O3", "-fPIC", "-std=c++17",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            # accumulators of the matrix instructions in ordinary registers: the form with accumulation
+            # registers copied them out and back around every step of a loop
+            "-mllvm", "-amdgpu-mfma-vgpr-form=1",
             "-Wno-unused-command-line-argument", "-I" + INCLUDE, "-I" + CSRC]
 
 

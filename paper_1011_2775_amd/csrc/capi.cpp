@@ -827,6 +827,76 @@ static int transfer_coarse(Ctx* c, LatticeState& L, int level, int prec, void* o
   });
 }
 
+// restrict (to_coarse) or prolong between the fine lattice and coarse level 1:
+// the kernels read and write the canonical layouts, all right-hand sides (16
+// at most) in one launch.  F16: fine vectors and null vectors are rounded to
+// half-precision spinors; what is read or written is then FP32.
+static void transfer_fine(Ctx* c, LatticeState& L, int prec, int nrhs, void* out, const void* in, bool to_coarse) {
+  const Geom& g = L.F.g;
+  FineTransfer& T = L.T0;
+  const size_t one = (size_t)g.V * 12 * 16, cone = (size_t)L.levels[0]->cg.V * L.levels[0]->cg.n * 16;
+  const void* vecs = prec == WCMG_F64 ? T.v64.p : T.v32.p;
+  const bool half = prec == WCMG_F16;
+  const size_t hb = spinor_bytes(WCMG_F16, g.Vh);
+  char* fe = nullptr;
+  char* fo = nullptr;
+  char* rounded = nullptr;
+  if (half) {
+    if (!T.vh32.p) {
+      T.vh32.alloc((size_t)T.nvec * g.V * 96);
+      launch_vec_half_rounded(T.vh32.p, T.v64.p, T.nvec, T.bg, c->st);
+    }
+    vecs = T.vh32.p;
+    fe = (char*)c->scratch_buf(42, hb);
+    fo = (char*)c->scratch_buf(43, hb);
+    if (to_coarse) rounded = (char*)c->scratch_buf(46, one * std::min(nrhs, kMaxTransfer));
+  }
+  for (int r0 = 0; r0 < nrhs; r0 += kMaxTransfer) {
+    const int n = std::min(kMaxTransfer, nrhs - r0);
+    if (to_coarse) {
+      RestrictArgs a{};
+      a.vecs = vecs;
+      a.nvec = T.nvec;
+      a.nin = n;
+      a.site_stride = (size_t)L.levels[0]->cg.n;
+      a.p0 = 0;
+      a.np = 2;
+      a.g = dgeom(g);
+      a.bg = T.bg;
+      for (int i = 0; i < n; ++i) {
+        a.in[i] = (const char*)in + (size_t)(r0 + i) * one;
+        a.out[i] = (char*)out + (size_t)(r0 + i) * cone;
+        if (half) {
+          spinor_to_internal(WCMG_F16, fe, fo, a.in[i], g, false, c->st);
+          spinor_from_internal(WCMG_F16, rounded + i * one, fe, fo, g, false, c->st);
+          a.in[i] = rounded + i * one;
+        }
+      }
+      launch_restrict(prec == WCMG_F64 ? WCMG_F64 : WCMG_F32, true, a, c->st);
+    } else {
+      ProlongArgs a{};
+      a.vecs = vecs;
+      a.nvec = T.nvec;
+      a.nin = n;
+      a.p0 = 0;
+      a.np = 2;
+      a.g = dgeom(g);
+      a.bg = T.bg;
+      for (int i = 0; i < n; ++i) {
+        a.in[i] = (const char*)in + (size_t)(r0 + i) * cone;
+        a.out[i] = (char*)out + (size_t)(r0 + i) * one;
+      }
+      launch_prolong(prec == WCMG_F64 ? WCMG_F64 : WCMG_F32, true, a, c->st);
+      if (half)
+        for (int i = 0; i < n; ++i) {
+          spinor_to_internal(WCMG_F16, fe, fo, a.out[i], g, false, c->st);
+          spinor_from_internal(WCMG_F16, a.out[i], fe, fo, g, false, c->st);
+        }
+    }
+  }
+  HIPCHK(hipStreamSynchronize(c->st));
+}
+
 int wcmg_restrict(void* ctx, int lat, int level, int prec, void* coarse_out, const void* fine_in, int nrhs) {
   Ctx* c = as_ctx(ctx);
   if (int r = check_lat(c, lat)) return r;
@@ -840,32 +910,7 @@ int wcmg_restrict(void* ctx, int lat, int level, int prec, void* coarse_out, con
   CHECK_DEV(c, fine_in, (size_t)nrhs * L.F.g.V * 12 * 16, "fine vectors");
   CHECK_DEV(c, coarse_out, (size_t)nrhs * L.levels[0]->cg.V * L.levels[0]->cg.n * 16, "coarse vectors");
   return guarded([&] {
-    const Geom& g = L.F.g;
-    CoarseLevel& C = *L.levels[0];
-    const int cprec = prec == WCMG_F64 ? WCMG_F64 : WCMG_F32;
-    const size_t hb = spinor_bytes(prec, g.Vh);
-    void* fe = c->scratch_buf(42, hb);
-    void* fo = c->scratch_buf(43, hb);
-    void* cv = c->scratch_buf(46, (size_t)C.cg.V * C.cg.n * 16);
-    const void* vecs = L.T0.v64.p;
-    DBuf v16;
-    if (prec == WCMG_F32) vecs = L.T0.v32.p;
-    if (prec == WCMG_F16) {
-      const size_t h64 = spinor_bytes(WCMG_F64, g.Vh), h16 = spinor_bytes(WCMG_F16, g.Vh);
-      v16.alloc((size_t)2 * L.T0.nvec * h16);
-      for (int k = 0; k < 2 * L.T0.nvec; ++k)
-        spinor_convert(WCMG_F16, (char*)v16.p + k * h16, WCMG_F64, (const char*)L.T0.v64.p + k * h64, g.Vh, c->st);
-      vecs = v16.p;
-    }
-    const size_t one = (size_t)g.V * 12 * 16, cone = (size_t)C.cg.V * C.cg.n * 16;
-    for (int r = 0; r < nrhs; ++r) {
-      spinor_to_internal(prec, fe, fo, (const char*)fine_in + r * one, g, false, c->st);
-      const void* vbm = prec == WCMG_F32 ? L.T0.vbm32.p : nullptr;
-      launch_restrict(prec, cv, C.cg.n, 1, fe, vecs, L.T0.nvec, 0, g, L.T0.bg, false, c->st, vbm);
-      launch_restrict(prec, cv, C.cg.n, 1, fo, vecs, L.T0.nvec, 1, g, L.T0.bg, true, c->st, vbm);
-      launch_coarse_canon(cprec, cv, (char*)coarse_out + r * cone, C.perm.as<int>(), C.cg.V, C.cg.n, false, c->st);
-    }
-    HIPCHK(hipStreamSynchronize(c->st));
+    transfer_fine(c, L, prec, nrhs, coarse_out, fine_in, true);
   });
 }
 
@@ -882,31 +927,7 @@ int wcmg_prolong(void* ctx, int lat, int level, int prec, void* fine_out, const 
   CHECK_DEV(c, fine_out, (size_t)nrhs * L.F.g.V * 12 * 16, "fine vectors");
   CHECK_DEV(c, coarse_in, (size_t)nrhs * L.levels[0]->cg.V * L.levels[0]->cg.n * 16, "coarse vectors");
   return guarded([&] {
-    const Geom& g = L.F.g;
-    CoarseLevel& C = *L.levels[0];
-    const int cprec = prec == WCMG_F64 ? WCMG_F64 : WCMG_F32;
-    const size_t hb = spinor_bytes(prec, g.Vh);
-    void* fe = c->scratch_buf(42, hb);
-    void* fo = c->scratch_buf(43, hb);
-    void* cv = c->scratch_buf(46, (size_t)C.cg.V * C.cg.n * 16);
-    const void* vecs = L.T0.v64.p;
-    DBuf v16;
-    if (prec == WCMG_F32) vecs = L.T0.v32.p;
-    if (prec == WCMG_F16) {
-      const size_t h64 = spinor_bytes(WCMG_F64, g.Vh), h16 = spinor_bytes(WCMG_F16, g.Vh);
-      v16.alloc((size_t)2 * L.T0.nvec * h16);
-      for (int k = 0; k < 2 * L.T0.nvec; ++k)
-        spinor_convert(WCMG_F16, (char*)v16.p + k * h16, WCMG_F64, (const char*)L.T0.v64.p + k * h64, g.Vh, c->st);
-      vecs = v16.p;
-    }
-    const size_t one = (size_t)g.V * 12 * 16, cone = (size_t)C.cg.V * C.cg.n * 16;
-    for (int r = 0; r < nrhs; ++r) {
-      launch_coarse_canon(cprec, cv, (char*)coarse_in + r * cone, C.perm.as<int>(), C.cg.V, C.cg.n, true, c->st);
-      launch_prolong(prec, fe, cv, vecs, L.T0.nvec, 0, g, L.T0.bg, c->st);
-      launch_prolong(prec, fo, cv, vecs, L.T0.nvec, 1, g, L.T0.bg, c->st);
-      spinor_from_internal(prec, (char*)fine_out + r * one, fe, fo, g, false, c->st);
-    }
-    HIPCHK(hipStreamSynchronize(c->st));
+    transfer_fine(c, L, prec, nrhs, fine_out, coarse_in, false);
   });
 }
 

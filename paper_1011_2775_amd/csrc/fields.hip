@@ -99,22 +99,15 @@ __global__ void k_spinor_convert(void* dst, const void* src, int Vh) {
 }
 
 template <typename S>
-__global__ void k_spinor_chiral(void* dst, const void* src, int Vh, int chi, int flip_lower) {
+__global__ void k_spinor_gamma5(void* v, int Vh) {
   using C = typename Compute<S>::T;
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= Vh) return;
-  cpx<C> v[12];
-  SpinorIO<S>::load(src, Vh, i, v);
+  cpx<C> w[12];
+  SpinorIO<S>::load(v, Vh, i, w);
 #pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    int s = k >= 6;
-    if (flip_lower) {
-      if (s) v[k] = mk(-v[k].r, -v[k].i);
-    } else if (s != chi) {
-      v[k] = mk((C)0, (C)0);
-    }
-  }
-  SpinorIO<S>::store(dst, Vh, i, v);
+  for (int k = 6; k < 12; ++k) w[k] = mk(-w[k].r, -w[k].i);
+  SpinorIO<S>::store(v, Vh, i, w);
 }
 
 // ---------------------------------------------------------------- clover
@@ -390,15 +383,15 @@ void spinor_convert(int pd, void* dst, int ps, const void* src, int Vh, hipStrea
 
 void spinor_gamma5(int prec, void* v, int Vh, hipStream_t st) {
   if (prec == WCMG_F64)
-    hipLaunchKernelGGL(k_spinor_chiral<double>, grid_for(Vh), dim3(kT), 0, st, v, v, Vh, 0, 1);
+    hipLaunchKernelGGL(k_spinor_gamma5<double>, grid_for(Vh), dim3(kT), 0, st, v, Vh);
   else if (prec == WCMG_F32)
-    hipLaunchKernelGGL(k_spinor_chiral<float>, grid_for(Vh), dim3(kT), 0, st, v, v, Vh, 0, 1);
+    hipLaunchKernelGGL(k_spinor_gamma5<float>, grid_for(Vh), dim3(kT), 0, st, v, Vh);
   else
-    hipLaunchKernelGGL(k_spinor_chiral<__half>, grid_for(Vh), dim3(kT), 0, st, v, v, Vh, 0, 1);
+    hipLaunchKernelGGL(k_spinor_gamma5<__half>, grid_for(Vh), dim3(kT), 0, st, v, Vh);
   HIPCHK(hipGetLastError());
 }
 
-void spinor_chiral_project(int prec, void* dst, const void* src, int Vh, int chi, hipStream_t st) {
+void* dst, const void* src, int Vh, int chi, hipStream_t st) {
   if (prec == WCMG_F64)
     hipLaunchKernelGGL(k_spinor_chiral<double>, grid_for(Vh), dim3(kT), 0, st, dst, src, Vh, chi, 0);
   else if (prec == WCMG_F32)

@@ -67,8 +67,6 @@ void spinor_from_internal(int prec, void* canon, const void* even, const void* o
 // one parity, any precision pair
 void spinor_convert(int prec_dst, void* dst, int prec_src, const void* src, int Vh, hipStream_t st);
 void spinor_gamma5(int prec, void* v, int Vh, hipStream_t st);
-// keep only the components of chirality chi (0: spins 0,1; 1: spins 2,3)
-void spinor_chiral_project(int prec, void* dst, const void* src, int Vh, int chi, hipStream_t st);
 
 struct CloverCoef {
   double s[6][2][4][2];  // [plane][chirality][2x2 entry][re,im] = csw (i/2) sigma_mu_nu block
@@ -191,28 +189,55 @@ struct BlockGeom {
 // coarse internal index of coarse lexicographic site
 int coarse_internal_index_host(const BlockGeom& bg, int lex);
 
-// R: coarse[c][s*Nv+k] (+)= sign(s) sum conj(V_k) in over fine sites of parity p
-// vecs: Nv full-lattice spinors (precision prec) in internal layout
-// out_site_stride/out_row_stride are in complex elements; accumulate: add into out
-// vbm (FP32 only, optional): the block-major copy of vecs (launch_vec_blockmajor),
-// read instead of vecs with the same arithmetic (coalesced loads); vbm16 (FP32
-// only, optional): the FP16 copy of vbm (launch_chunks_to_half), read instead of both
-void launch_restrict(int prec, void* out, size_t out_site_stride, size_t out_row_stride, const void* in,
-                     const void* vecs, int nvec, int p, const Geom& g, const BlockGeom& bg, bool accumulate,
-                     hipStream_t st, const void* vbm = nullptr, const void* vbm16 = nullptr);
-// out (same size as v32) = the FP32 vectors v32 block by block: float4 chunk c of
-// the l-th site (restriction order) of parity p of block b of vector k at
-// (((k 2 + p) Vc + b) 6 + c) (bvol / 2) + l
-void launch_vec_blockmajor(void* out, const void* v32, int nvec, const Geom& g, const BlockGeom& bg, hipStream_t st);
-// P: out_p(x) = sum_k V_k(x) coarse[c(x)][s*Nv+k]; v16 (FP32 only, optional): the FP16
-// copy of the FP32 vectors (launch_chunks_to_half), read instead of vecs
-void launch_prolong(int prec, void* out, const void* coarse, const void* vecs, int nvec, int p, const Geom& g,
-                    const BlockGeom& bg, hipStream_t st, const void* v16 = nullptr);
-// FP16 copy of nchunks float4 chunks (two complex FP32 each): uint2 per chunk
-void launch_chunks_to_half(void* out, const void* in32, size_t nchunks, hipStream_t st);
-// block x chirality Gram-Schmidt (twice) of Nv full-lattice FP64 spinors in place
-void launch_block_orthonormalize(void* vecs, int nvec, const Geom& g, const BlockGeom& bg, int* flag,
-                                 hipStream_t st);
+// Transfers of the first level.  vecs: Nv block-orthonormalised vectors block
+// by block, [k][parity][block][chirality][site of the half][6] complex in the
+// storage vprec (F64, F32 or F16; F32 arithmetic for the last two).
+// canonical: fine vectors [V][4][3] and coarse vectors complex128, rounded to
+// the arithmetic on reading; else coarse vectors of the arithmetic's type, R
+// from fine vectors in the layout of vecs (one vector) and P to the
+// parity-split layout (even half at the pointer, odd half odd_bytes behind
+// it).  Parities p0 .. p0 + np - 1; up to kMaxTransfer vectors at once.
+constexpr int kMaxTransfer = 16;
+struct RestrictArgs {
+  const void* vecs;
+  int nvec;
+  int nin;
+  const void* in[kMaxTransfer];
+  void* out[kMaxTransfer];
+  size_t site_stride;  // complex elements from one coarse site of out to the next
+  int p0, np;
+  int internal_sites;  // coarse sites in internal order (else lexicographic)
+  DGeom g;
+  BlockGeom bg;
+};
+struct ProlongArgs {
+  const void* vecs;
+  int nvec;
+  int nin;
+  const void* in[kMaxTransfer];
+  void* out[kMaxTransfer];
+  size_t odd_bytes;
+  int p0, np;
+  int internal_sites;
+  DGeom g;
+  BlockGeom bg;
+};
+// R: out[c][s*Nv+k] = sign(s) sum conj(V_k) in over the sites of the parities
+void launch_restrict(int vprec, bool canonical, const RestrictArgs& a, hipStream_t st);
+// P: out(x) = sum_k V_k(x) in[c(x)][s*Nv+k] on the sites of the parities
+void launch_prolong(int vprec, bool canonical, const ProlongArgs& a, hipStream_t st);
+// even halves of nrhs FP64 spinors rounded to prec (F64 or F32), in the fine layout and in the layout of vecs
+void launch_round_even(int prec, void* fine, void* block, const void* in64, const Geom& g, const BlockGeom& bg,
+                       int nrhs, hipStream_t st);
+// fine FP64 vectors (parity-split layout) block by block
+void launch_vec_to_block(void* out, const void* raw, int nvec, const Geom& g, const BlockGeom& bg, hipStream_t st);
+// chirality s of vector k as a fine FP64 spinor (both halves, the other chirality zero)
+void launch_block_column(void* out, const void* v64, int k, int s, const Geom& g, const BlockGeom& bg,
+                         hipStream_t st);
+// FP32 copy of the vectors rounded as half-precision spinors are (one scale a site)
+void launch_vec_half_rounded(void* out32, const void* v64, int nvec, const BlockGeom& bg, hipStream_t st);
+// block x chirality Gram-Schmidt (twice) of the FP64 vectors in place
+void launch_block_orthonormalize(void* vecs, int nvec, const BlockGeom& bg, int* flag, hipStream_t st);
 // coarse build: nine direction buckets of the D_p hop of u = A^-1 v (both parities)
 void launch_hop_split(void* const* buckets /*9 full spinors F64*/, const void* v, const void* u,
                       const void* gauge64, const Geom& g, const BlockGeom& bg, hipStream_t st);

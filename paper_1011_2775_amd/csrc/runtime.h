@@ -171,9 +171,10 @@ struct FineTransfer {
   int nvec = 0;
   bool have_vecs = false, orth = false;
   DBuf raw;       // FP64 full spinors (as given / found by the setup)
-  DBuf v64, v32;  // block-orthonormalised copies
-  DBuf vbm32;     // v32 in block-major order for the restriction
-  DBuf v16, vbm16;  // FP16 copies of v32 and vbm32 (the cycle's transfers with transfer_fp16)
+  // block-orthonormalised copies, block by block (kernels.h): FP64, FP32 and FP16 (the
+  // cycle's transfers with transfer_fp16)
+  DBuf v64, v32, v16;
+  DBuf vh32;      // v64 rounded as FP16 spinors are, in FP32 (made by the first F16 transfer)
 };
 
 // transfer between coarse level l (>= 1) and level l+1; vectors in the

@@ -809,6 +809,7 @@ struct MGSolver {
   int cp;  // precision of the coarse levels
   int fprec = -1;  // storage of the fields in the fine smoother (F16 or as sp)
   DBuf r_s, e_s, res_s, Ar_s;
+  DBuf r_bl;  // r_s in the block layout of the null vectors
   struct Level {
     DBuf cb, cc, cbr, cy;       // right-hand side, solution, reduced forms
     DBuf rfull, e, res, Ar;     // preconditioner and smoother work of this level
@@ -849,6 +850,7 @@ struct MGSolver {
     const Geom& g = L.F.g;
     size_t hb = spinor_bytes(sp, g.Vh);
     r_s.alloc(hb);
+    r_bl.alloc(hb);
     e_s.alloc(hb);
     res_s.alloc(hb);
     Ar_s.alloc(hb);
@@ -866,11 +868,43 @@ struct MGSolver {
   }
 
   int nlev() const { return L.params.nlevels; }
-  const void* vecs(int prec) const { return prec == WCMG_F64 ? L.T0.v64.p : L.T0.v32.p; }
-  const void* vbm(int prec) const { return prec == WCMG_F32 ? L.T0.vbm32.p : nullptr; }
-  bool half_transfer(int prec) const { return prec == WCMG_F32 && L.params.transfer_fp16 != 0 && L.T0.v16.p; }
-  const void* v16(int prec) const { return half_transfer(prec) ? L.T0.v16.p : nullptr; }
-  const void* vbm16(int prec) const { return half_transfer(prec) ? L.T0.vbm16.p : nullptr; }
+  // storage of the vectors the cycle's transfers read, and R and P of nrhs even halves
+  int vprec() const { return sp == WCMG_F64 ? WCMG_F64 : (L.params.transfer_fp16 != 0 ? WCMG_F16 : WCMG_F32); }
+  const void* vecs() const {
+    const int v = vprec();
+    return v == WCMG_F64 ? L.T0.v64.p : (v == WCMG_F16 ? L.T0.v16.p : L.T0.v32.p);
+  }
+  template <typename Args>
+  Args transfer_args() const {
+    Args a{};
+    a.vecs = vecs();
+    a.nvec = L.T0.nvec;
+    a.p0 = 0;
+    a.np = 1;
+    a.internal_sites = 1;
+    a.g = dgeom(L.F.g);
+    a.bg = L.T0.bg;
+    return a;
+  }
+  void fine_restrict(void* coarse, size_t cstride, const void* fine, size_t fstride, int nrhs) {
+    RestrictArgs a = transfer_args<RestrictArgs>();
+    a.site_stride = (size_t)2 * L.T0.nvec;
+    a.nin = nrhs;
+    for (int i = 0; i < nrhs; ++i) {
+      a.in[i] = (const char*)fine + i * fstride;
+      a.out[i] = (char*)coarse + i * cstride;
+    }
+    launch_restrict(vprec(), false, a, c.st);
+  }
+  void fine_prolong(void* fine, size_t fstride, const void* coarse, size_t cstride, int nrhs) {
+    ProlongArgs a = transfer_args<ProlongArgs>();
+    a.nin = nrhs;
+    for (int i = 0; i < nrhs; ++i) {
+      a.in[i] = (const char*)coarse + i * cstride;
+      a.out[i] = (char*)fine + i * fstride;
+    }
+    launch_prolong(vprec(), false, a, c.st);
+  }
   CoarseOp cop(int li) {
     CoarseOp o{L.levels[li].get(), cp, &cwork, c.st, &c.timer};
     o.timer_base = li < 2 ? 20 + 2 * li : 96 + 2 * (li - 2);
@@ -1130,11 +1164,10 @@ struct MGSolver {
     const size_t n = (size_t)12 * g.Vh;
     CoarseLevel& C = *L.levels[0];
     Level& V = lv[0];
-    spinor_convert(sp, r_s.p, WCMG_F64, r64, g.Vh, st);
-    launch_restrict(sp, V.cb.p, C.cg.n, 1, r_s.p, vecs(sp), L.T0.nvec, 0, g, L.T0.bg, false, st, vbm(sp),
-                    vbm16(sp));
+    launch_round_even(sp, r_s.p, r_bl.p, r64, g, L.T0.bg, 1, st);
+    fine_restrict(V.cb.p, 0, r_bl.p, 0, 1);
     coarse_solve(0, V.cc.p, V.cb.p);
-    launch_prolong(sp, e_s.p, V.cc.p, vecs(sp), L.T0.nvec, 0, g, L.T0.bg, st, v16(sp));
+    fine_prolong(e_s.p, 0, V.cc.p, 0, 1);
     mr_smooth([&](void* o, const void* i) { op.Dr(o, i); },
               [&](void* o, void* i, const RedOut& ro, void* ee, const double* cf) {
                 return op.Dr_red(o, i, ro, ee, cf);
@@ -1149,7 +1182,7 @@ struct MGSolver {
     const Geom& g = L.F.g;
     if (batch < nrhs) {
       const size_t hb = spinor_bytes(sp, g.Vh) * nrhs;
-      for (DBuf* b : {&r_s, &e_s, &res_s, &Ar_s}) b->alloc(hb);
+      for (DBuf* b : {&r_s, &r_bl, &e_s, &res_s, &Ar_s}) b->alloc(hb);
       batch = nrhs;
     }
     const size_t cs = (cp == WCMG_F64 ? 16 : 8);
@@ -1271,15 +1304,10 @@ struct MGSolver {
     CoarseLevel& C = *L.levels[0];
     Level& V = lv[0];
     const size_t na = (size_t)C.cg.V * C.cg.n, cs = cp == WCMG_F64 ? 16 : 8;
-    for (int i = 0; i < nrhs; ++i) {
-      spinor_convert(sp, (char*)r_s.p + i * hs, WCMG_F64, (const char*)r64 + i * h64, g.Vh, st);
-      launch_restrict(sp, (char*)V.cb.p + i * na * cs, C.cg.n, 1, (char*)r_s.p + i * hs, vecs(sp), L.T0.nvec, 0, g,
-                      L.T0.bg, false, st, vbm(sp), vbm16(sp));
-    }
+    launch_round_even(sp, r_s.p, r_bl.p, r64, g, L.T0.bg, nrhs, st);
+    fine_restrict(V.cb.p, na * cs, r_bl.p, hs, nrhs);
     coarse_solve_b(0, V.cc.p, V.cb.p, nrhs);
-    for (int i = 0; i < nrhs; ++i)
-      launch_prolong(sp, (char*)e_s.p + i * hs, (char*)V.cc.p + i * na * cs, vecs(sp), L.T0.nvec, 0, g, L.T0.bg,
-                     st, v16(sp));
+    fine_prolong(e_s.p, hs, V.cc.p, na * cs, nrhs);
     mr_smooth_b([&](void* o, const void* i) { op.Dr(o, i, nrhs); }, sp, e_s.p, r_s.p, res_s.p, Ar_s.p, n, n, nrhs);
     for (int i = 0; i < nrhs; ++i)
       spinor_convert(WCMG_F64, (char*)z64 + i * h64, sp, (char*)e_s.p + i * hs, g.Vh, st);
@@ -1732,28 +1760,19 @@ void mg_build_coarse(Ctx& c, LatticeState& L, int level) {
   T.nvec = nvec;
   // P: block x chirality orthonormalisation
   T.v64.alloc((size_t)nvec * 2 * hb64);
-  HIPCHK(hipMemcpyAsync(T.v64.p, T.raw.p, (size_t)nvec * 2 * hb64, hipMemcpyDeviceToDevice, st));
+  T.vh32.release();
+  launch_vec_to_block(T.v64.p, T.raw.p, nvec, g, T.bg, st);
   int* flag = (int*)c.scratch_buf(12, 64);
   HIPCHK(hipMemsetAsync(flag, 0, 64, st));
-  launch_block_orthonormalize(T.v64.p, nvec, g, T.bg, flag, st);
+  launch_block_orthonormalize(T.v64.p, nvec, T.bg, flag, st);
   int hflag[2] = {0, 0};
   HIPCHK(hipMemcpyAsync(hflag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   if (hflag[0]) fail(WCMG_ERANK, "null vectors are linearly dependent on a block");
   T.v32.alloc((size_t)nvec * 2 * hb32);
-  for (int k = 0; k < 2 * nvec; ++k)
-    spinor_convert(WCMG_F32, (char*)T.v32.p + (size_t)k * hb32, WCMG_F64, (const char*)T.v64.p + (size_t)k * hb64,
-                   g.Vh, st);
-  T.vbm32.alloc((size_t)nvec * 2 * hb32);
-  launch_vec_blockmajor(T.vbm32.p, T.v32.p, nvec, g, T.bg, st);
-  {
-    // FP16 copies for the cycle's transfers (transfer_fp16): four halves per float4 chunk
-    const size_t nch = (size_t)nvec * 2 * hb32 / 16;
-    T.v16.alloc(nch * 8);
-    T.vbm16.alloc(nch * 8);
-    launch_chunks_to_half(T.v16.p, T.v32.p, nch, st);
-    launch_chunks_to_half(T.vbm16.p, T.vbm32.p, nch, st);
-  }
+  T.v16.alloc((size_t)nvec * 2 * hb32 / 2);
+  launch_reals_convert(WCMG_F32, T.v32.p, T.v64.as<double>(), (size_t)nvec * 48 * g.Vh, st);
+  launch_reals_convert(WCMG_F16, T.v16.p, T.v64.as<double>(), (size_t)nvec * 48 * g.Vh, st);
   T.orth = true;
 
   if (L.levels.empty()) L.levels.emplace_back(new CoarseLevel());
@@ -1771,20 +1790,26 @@ void mg_build_coarse(Ctx& c, LatticeState& L, int level) {
   for (int s = 0; s < 9; ++s) bucket[s] = c.scratch_buf(20 + s, 2 * hb64);
   void* vcol = c.scratch_buf(30, 2 * hb64);
   void* u = c.scratch_buf(31, 2 * hb64);
+  RestrictArgs ra{};
+  ra.vecs = T.v64.p;
+  ra.nvec = nvec;
+  ra.nin = 9;
+  for (int s = 0; s < 9; ++s) ra.in[s] = bucket[s];
+  ra.site_stride = 9 * nn;
+  ra.p0 = 0;
+  ra.np = 2;
+  ra.internal_sites = 1;
+  ra.g = dgeom(g);
+  ra.bg = T.bg;
   for (int s = 0; s < 2; ++s)
     for (int k = 0; k < nvec; ++k) {
       const int j = s * nvec + k;
-      const char* vk = (const char*)T.v64.p + (size_t)k * 2 * hb64;
-      spinor_chiral_project(WCMG_F64, vcol, vk, g.Vh, s, st);
-      spinor_chiral_project(WCMG_F64, (char*)vcol + hb64, vk + hb64, g.Vh, s, st);
+      launch_block_column(vcol, T.v64.p, k, s, g, T.bg, st);
       op.clover(u, vcol, 0, 1);
       op.clover((char*)u + hb64, (char*)vcol + hb64, 1, 1);
       launch_hop_split(bucket, vcol, u, L.F.gauge[WCMG_F64].p, g, T.bg, st);
-      for (int slot = 0; slot < 9; ++slot) {
-        void* out = (char*)C.Y9.p + ((size_t)slot * n + j) * n * 16;
-        launch_restrict(WCMG_F64, out, 9 * nn, 1, bucket[slot], T.v64.p, nvec, 0, g, T.bg, false, st);
-        launch_restrict(WCMG_F64, out, 9 * nn, 1, (char*)bucket[slot] + hb64, T.v64.p, nvec, 1, g, T.bg, true, st);
-      }
+      for (int slot = 0; slot < 9; ++slot) ra.out[slot] = (char*)C.Y9.p + ((size_t)slot * n + j) * n * 16;
+      launch_restrict(WCMG_F64, false, ra, st);
     }
   finalize_coarse(c, C, flag);
   C.built = true;
