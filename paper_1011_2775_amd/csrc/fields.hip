@@ -391,16 +391,6 @@ void spinor_gamma5(int prec, void* v, int Vh, hipStream_t st) {
   HIPCHK(hipGetLastError());
 }
 
-void* dst, const void* src, int Vh, int chi, hipStream_t st) {
-  if (prec == WCMG_F64)
-    hipLaunchKernelGGL(k_spinor_chiral<double>, grid_for(Vh), dim3(kT), 0, st, dst, src, Vh, chi, 0);
-  else if (prec == WCMG_F32)
-    hipLaunchKernelGGL(k_spinor_chiral<float>, grid_for(Vh), dim3(kT), 0, st, dst, src, Vh, chi, 0);
-  else
-    hipLaunchKernelGGL(k_spinor_chiral<__half>, grid_for(Vh), dim3(kT), 0, st, dst, src, Vh, chi, 0);
-  HIPCHK(hipGetLastError());
-}
-
 void clover_compute(void* clov64, const void* gauge64, const Geom& g, double m0, const CloverCoef& cc, int* flag,
                     hipStream_t st) {
   hipLaunchKernelGGL(k_clover, grid_for(g.V, 128), dim3(128), 0, st, reinterpret_cast<double*>(clov64),
