@@ -65,6 +65,14 @@ def clover_bytes_per_site(prec):
     return b + (8 if prec == 2 else 0)
 
 
+def canonical_bytes(prec, form):
+    """Bytes per even site and right-hand side that the launches of an apply move for the caller's canonical
+    complex128 spinors in place of the internal ones, [launch of the clover inverse, last hop]: the clover launch
+    of D_r ("schur") reads the input and the last hop reads it again, the last hop writes both sites of a pair."""
+    inner = 24 * real_size(prec) + (4 if prec == 2 else 0)
+    return [192 - inner, 192 - inner + 384 - inner] if form == "schur" else [0, 384 - inner]
+
+
 def dr_compulsory_bytes(prec, nrhs=1):
     """Compulsory bytes of D_r per even site and right-hand side: five spinor
     passes (y read twice is counted once per kernel that needs it: y, the
@@ -296,7 +304,9 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
     with the diagonal input fused) and D_r D_ee (two launches: hop with
     D_oo^-1 fused, hop with D_ee x fused), every launch of an apply timed with
     HIP events on the library stream; bandwidth from the compulsory bytes of
-    the reduced operator (dr_compulsory_bytes), which both forms share.
+    the reduced operator (dr_compulsory_bytes), which both forms share, plus
+    what the launches move for the caller's canonical spinors
+    (canonical_bytes).
     Protocol: 10 warm-up applies, then 5 trials of 40 applies (12 right-hand
     sides: 3 trials of 10), the median trial."""
     U = inputs.gauge_field_torch(dims, 0.5, 1003, device="cuda")
@@ -322,14 +332,16 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
                     ids = [base + prec * 6 + 1, base + prec * 6 + 2, (67 if batch else 64) + prec]
                     names = ["dslash_kernel<%s,0,true>" % PREC_NAMES[prec],
                              "dslash_kernel<%s,1,false>" % PREC_NAMES[prec], "clover_kernel<%s>" % PREC_NAMES[prec]]
-                    nbs = [dslash_bytes_per_site(prec, 0, True), dslash_bytes_per_site(prec, 1, False),
-                           clover_bytes_per_site(prec)]
+                    canon = canonical_bytes(prec, "schur")
+                    nbs = [dslash_bytes_per_site(prec, 0, True), dslash_bytes_per_site(prec, 1, False) + canon[1],
+                           clover_bytes_per_site(prec) + canon[0]]
                 else:
                     # hop with A_oo^-1 fused (odd), hop with A_ee x fused (even)
                     ids = [base + prec * 6 + 1, base + prec * 6 + 4]
                     names = ["dslash_kernel<%s,0,true>" % PREC_NAMES[prec],
                              "dslash_kernel<%s,2,false>" % PREC_NAMES[prec]]
-                    nbs = [dslash_bytes_per_site(prec, 0, True), dslash_bytes_per_site(prec, 2, False)]
+                    canon = canonical_bytes(prec, "schur_x")
+                    nbs = [dslash_bytes_per_site(prec, 0, True), dslash_bytes_per_site(prec, 2, False) + canon[1]]
                 trials = []
                 for _ in range(3 if batch else 5):
                     ctx.timer_enable(True)
@@ -344,7 +356,7 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
                     trials.append((tot_ms, per, napply))
                 trials.sort(key=lambda t: t[0])
                 tot_ms, per, napply = trials[len(trials) // 2]
-                comp = dr_compulsory_bytes(prec, nrhs) * nrhs * vh
+                comp = (dr_compulsory_bytes(prec, nrhs) + sum(canon)) * nrhs * vh
                 gbps = comp / (tot_ms * 1e-3) / 1e9
                 kern = []
                 for kid, nm, nb in zip(ids, names, nbs):
@@ -362,6 +374,7 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
                 rec = {"form": "D_r, 3 launches" if op == w.OP_SCHUR else "D_r D_ee (variable x = D_ee^-1 y), "
                        "2 launches", "dr_us": round(tot_ms * 1e3, 2),
                        "compulsory_bytes_per_even_site_per_rhs": round(dr_compulsory_bytes(prec, nrhs), 1),
+                       "canonical_bytes_per_even_site_per_rhs": sum(canon),
                        "GBps": round(gbps, 1), "frac_of_8TBps": round(gbps / PEAK_HBM_GBS, 3), "kernels": kern,
                        "trials_us": [round(t[0] * 1e3, 2) for t in trials]}
                 if ceiling:

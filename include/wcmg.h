@@ -367,8 +367,9 @@ int wcmg_force(void* ctx, int lat, void* dU, const void* psi, const void* lam, i
 /* Project autotuner (on != 0: enable, 0: disable; choices are kept): the
  * first launch of each fine hop kernel variant for a given lattice,
  * precision and batch size times every candidate launch shape (64/128/256
- * threads per block x 1/2/4 right-hand sides per thread, or -1: one per
- * thread with the workgroups of a site block's right-hand sides adjacent) on the context
+ * threads per block; several right-hand sides 1: one per thread, -1: one per
+ * thread with the workgroups of a site block's right-hand sides adjacent, -2:
+ * two per thread, so arranged, in tiles of the lattice) on the context
  * stream and keeps the fastest.  Every candidate gives bitwise the same
  * result, so tuning never changes an answer.  Not during graph capture. */
 int wcmg_autotune(void* ctx, int on);

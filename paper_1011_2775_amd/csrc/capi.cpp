@@ -727,53 +727,9 @@ static int apply_common(void* ctx, int lat, int op, int prec, void* out, const v
   CHECK_DEV(c, in, (size_t)nrhs * L.F.g.V * 12 * 16, "input spinors");
   CHECK_DEV(c, out, (size_t)nrhs * L.F.g.V * 12 * 16, "output spinors");
   return guarded([&] {
-    const Geom& g = L.F.g;
-    const size_t hb = spinor_bytes(prec, g.Vh);
-    const size_t one = (size_t)g.V * 12 * 16;
     // all right-hand sides go through each kernel in one batched launch
-    char* ie = (char*)c->scratch_buf(42, hb * nrhs);
-    char* io = (char*)c->scratch_buf(43, hb * nrhs);
-    char* oe = (char*)c->scratch_buf(44, hb * nrhs);
-    char* oo = (char*)c->scratch_buf(45, hb * nrhs);
     FineOp fo{c, &L.F, prec, &c->fw[prec], c->st};
-    for (int r = 0; r < nrhs; ++r)
-      spinor_to_internal(prec, ie + r * hb, io + r * hb, (const char*)in + (size_t)r * one, g,
-                         dag && op != WCMG_OP_SCHUR, c->st);
-    bool flip_out = false;
-    char* re = oe;
-    char* ro = oo;
-    if (op == WCMG_OP_FULL) {
-      fo.D(oe, oo, ie, io, nrhs);
-      flip_out = dag;
-    } else if (op == WCMG_OP_DP) {
-      if (!dag) {
-        fo.Dp(oe, oo, ie, io, nrhs);
-      } else {
-        // D_p^dag = A^-1 gamma5 D gamma5
-        fo.D(oe, oo, ie, io, nrhs);
-        for (int r = 0; r < nrhs; ++r) {
-          spinor_gamma5(prec, oe + r * hb, g.Vh, c->st);
-          spinor_gamma5(prec, oo + r * hb, g.Vh, c->st);
-        }
-        fo.clover(ie, oe, 0, 1, nrhs);
-        fo.clover(io, oo, 1, 1, nrhs);
-        re = ie;
-        ro = io;
-      }
-    } else if (op == WCMG_OP_SCHUR_X) {
-      fo.Mx(oe, ie, nrhs);  // adjoint: input converted with gamma5 above, output flipped below
-      flip_out = dag;
-      ro = nullptr;
-    } else {
-      if (!dag)
-        fo.Dr(oe, ie, nrhs);
-      else
-        fo.Dr_dag(oe, ie, nrhs);
-      ro = nullptr;
-    }
-    for (int r = 0; r < nrhs; ++r)
-      spinor_from_internal(prec, (char*)out + (size_t)r * one, re + r * hb, ro ? ro + r * hb : nullptr, g, flip_out,
-                           c->st);
+    fo.apply(op, dag, out, in, nrhs);
   });
 }
 
@@ -1102,26 +1058,18 @@ static int solve_lattice(void* ctx, int lat, int solver, void* x, const void* b,
       for (int r0 = 0; r0 < nrhs; r0 += kMaxBatch) {
         const int nb = std::min(kMaxBatch, nrhs - r0);
         bool x_zero = true;
+        // D^dag x = b  <=>  D (gamma5 x) = gamma5 b
+        spinor_to_internal(WCMG_F64, be, bo, (const char*)b + (size_t)r0 * one, g, dag, c->st, nb);
+        spinor_to_internal(WCMG_F64, xe, xo, (const char*)x + (size_t)r0 * one, g, dag, c->st, nb);
         for (int i = 0; i < nb; ++i) {
-          const void* bs = (const char*)b + (size_t)(r0 + i) * one;
-          void* xs = (char*)x + (size_t)(r0 + i) * one;
-          spinor_to_internal(WCMG_F64, be + i * hb, bo + i * hb, bs, g, false, c->st);
-          spinor_to_internal(WCMG_F64, xe + i * hb, xo + i * hb, xs, g, false, c->st);
-          if (dag)
-            for (char* v : {be, bo, xe, xo}) spinor_gamma5(WCMG_F64, v + i * hb, g.Vh, c->st);
           x_zero = x_zero && norm2(*c, WCMG_F64, xe + i * hb, (size_t)12 * g.Vh) +
                                      norm2(*c, WCMG_F64, xo + i * hb, (size_t)12 * g.Vh) ==
                                  0.0;
         }
         std::vector<wcmg_stats> s(nb);
         solve_batch(*c, L, xe, xo, be, bo, nb, x_zero, tol, s.data());
+        spinor_from_internal(WCMG_F64, (char*)x + (size_t)r0 * one, xe, xo, g, dag, c->st, nb);
         for (int i = 0; i < nb; ++i) {
-          if (dag) {
-            spinor_gamma5(WCMG_F64, xe + i * hb, g.Vh, c->st);
-            spinor_gamma5(WCMG_F64, xo + i * hb, g.Vh, c->st);
-          }
-          spinor_from_internal(WCMG_F64, (char*)x + (size_t)(r0 + i) * one, xe + i * hb, xo + i * hb, g, false,
-                               c->st);
           if (stats) stats[r0 + i] = s[i];
           if (s[i].status != WCMG_OK && worst == WCMG_OK) worst = s[i].status;
         }
@@ -1136,20 +1084,13 @@ static int solve_lattice(void* ctx, int lat, int solver, void* x, const void* b,
     for (int r = 0; r < nrhs; ++r) {
       const void* bs = (const char*)b + (size_t)r * one;
       void* xs = (char*)x + (size_t)r * one;
-      spinor_to_internal(WCMG_F64, be, bo, bs, g, false, c->st);
-      spinor_to_internal(WCMG_F64, xe, xo, xs, g, false, c->st);
-      if (dag) {
-        // D^dag x = b  <=>  D (gamma5 x) = gamma5 b
-        for (void* v : {be, bo, xe, xo}) spinor_gamma5(WCMG_F64, v, g.Vh, c->st);
-      }
+      // D^dag x = b  <=>  D (gamma5 x) = gamma5 b
+      spinor_to_internal(WCMG_F64, be, bo, bs, g, dag, c->st);
+      spinor_to_internal(WCMG_F64, xe, xo, xs, g, dag, c->st);
       double xn = norm2(*c, WCMG_F64, xe, (size_t)12 * g.Vh) + norm2(*c, WCMG_F64, xo, (size_t)12 * g.Vh);
       wcmg_stats s{};
       solve_rhs(*c, L, solver, xe, xo, be, bo, xn == 0.0, tol, &s);
-      if (dag) {
-        spinor_gamma5(WCMG_F64, xe, g.Vh, c->st);
-        spinor_gamma5(WCMG_F64, xo, g.Vh, c->st);
-      }
-      spinor_from_internal(WCMG_F64, xs, xe, xo, g, false, c->st);
+      spinor_from_internal(WCMG_F64, xs, xe, xo, g, dag, c->st);
       if (stats) stats[r] = s;
       if (s.status != WCMG_OK && worst == WCMG_OK) worst = s.status;
     }

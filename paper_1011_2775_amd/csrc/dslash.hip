@@ -24,6 +24,8 @@
 #include "hop_core.h"
 #include "blas_common.h"
 
+#include <type_traits>
+
 namespace wcmg {
 
 // The direction terms are pure arithmetic, so the compiler is free to sink
@@ -48,14 +50,23 @@ __device__ __forceinline__ float to_f_or_d<__half, float>(__half v) {
   return __half2float(v);
 }
 
+// Site of place i when the sites are visited in tiles of tile_z x tile_t whole
+// x-y planes
+__device__ __forceinline__ int tile_site(const DslashArgs& a, int i) {
+  const int A = a.g.Lxh * a.g.L[1], pl = i / A, per = a.tile_z * a.tile_t, tile = pl / per, q = pl - tile * per;
+  const int nz = a.g.L[2] / a.tile_z;
+  const int z = (tile % nz) * a.tile_z + q % a.tile_z, t = (tile / nz) * a.tile_t + q / a.tile_z;
+  return (t * a.g.L[2] + z) * A + (i - pl * A);
+}
+
 template <typename S>
 __device__ __forceinline__ const void* rhs_ptr(const void* base, size_t stride, int r) {
   return reinterpret_cast<const char*>(base) + (size_t)r * stride;
 }
 
 template <typename S, typename G, int MU, int NR, bool STREAM, bool PIN = true>
-__device__ __forceinline__ void hop_mu(const DslashArgs& a, int p, int i, const int c[4], int g0, int nr,
-                                       cpx<typename Compute<S>::T> (&acc)[NR][12]) {
+__device__ __forceinline__ void hop_mu(const DslashArgs& a, const void* in, int p, int i, const int c[4], int g0,
+                                       int nr, cpx<typename Compute<S>::T> (&acc)[NR][12]) {
   using C = typename Compute<S>::T;
   const DGeom& g = a.g;
   cpx<C> psi[12], h[6], hu[6], U[9];
@@ -69,7 +80,7 @@ __device__ __forceinline__ void hop_mu(const DslashArgs& a, int p, int i, const 
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if (r < nr) {
-        SpinorIO<S>::load(rhs_ptr<S>(a.in, a.rstride, g0 + r), g.Vh, nb, psi);
+        SpinorIO<S>::load(rhs_ptr<S>(in, a.rstride, g0 + r), g.Vh, nb, psi);
         project<C, MU, false>(psi, h);
         link_mul<C, false>(U, h, hu);
         if (edge) {
@@ -97,7 +108,7 @@ __device__ __forceinline__ void hop_mu(const DslashArgs& a, int p, int i, const 
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if (r < nr) {
-        SpinorIO<S>::load(rhs_ptr<S>(a.in, a.rstride, g0 + r), g.Vh, nb, psi);
+        SpinorIO<S>::load(rhs_ptr<S>(in, a.rstride, g0 + r), g.Vh, nb, psi);
         project<C, MU, true>(psi, h);
         link_mul<C, true>(U, h, hu);
         if (edge) {
@@ -217,20 +228,119 @@ __device__ __forceinline__ void clover_multi(const void* clov, int Vh, int p, in
   }
 }
 
+// Spinors of the caller's canonical layout read and written in place of a
+// converted copy, with the rounding that storing them in S would give.
+template <typename S>
+__device__ __forceinline__ void load_canon(const double2* site, bool g5, cpx<typename Compute<S>::T> v[12]) {
+  using C = typename Compute<S>::T;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const double2 t = site[k];
+    const C sg = (g5 && k >= 6) ? (C)-1 : (C)1;
+    v[k] = mk((C)(sg * t.x), (C)(sg * t.y));
+  }
+  if constexpr (sizeof(S) == 2) round_half_spinor(v);
+}
+// A wavefront's sites leave together: through LDS, so that its lanes write
+// consecutive 16-byte pieces of the sites' rows (a site a lane writes pieces
+// 384 bytes apart, and the last hop of D_r A_ee for 12 FP32 right-hand sides
+// took 1285 us at 24^3x64 where it now takes 899).  zero: the other site of each x pair
+// (the other parity) is written too, with zeros.  All lanes take part; `count`
+// of them hold a site.  FP64 goes in two passes of six components (LDS).
+template <typename S>
+struct CanonTile {
+  using C = typename Compute<S>::T;
+  static constexpr int H = sizeof(S) == 8 ? 6 : 12;  // components a pass
+  cpx<C> v[4][64][H + 1];
+  int pair[4][64];
+};
+template <typename S>
+__device__ __forceinline__ void store_canon(CanonTile<S>& sh, double2* canon, int lex, int count, bool g5, bool zero,
+                                            cpx<typename Compute<S>::T> v[12]) {
+  constexpr int H = CanonTile<S>::H;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if constexpr (sizeof(S) == 2) round_half_spinor(v);
+  auto& tile = sh.v[wave];
+  sh.pair[wave][lane] = lex;
+#pragma unroll
+  for (int h = 0; h < 12; h += H) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < H; ++k) tile[lane][k] = v[h + k];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (zero) {
+      // pieces of both sites of a pair, H of each
+      for (int q = lane; q < count * 2 * H; q += 64) {
+        const int s = q / (2 * H), c = q - s * 2 * H, x = c >= H, k = c - x * H;
+        const int l = sh.pair[wave][s];
+        const double sg = (g5 && h + k >= 6) ? -1.0 : 1.0;
+        double2 o = make_double2(0.0, 0.0);
+        if ((l & 1) == x) {
+          const auto t = tile[s][k];
+          o = make_double2(sg * (double)t.r, sg * (double)t.i);
+        }
+        canon[(size_t)((l & ~1) + x) * 12 + h + k] = o;
+      }
+    } else {
+      for (int q = lane; q < count * H; q += 64) {
+        const int s = q / H, k = q - s * H;
+        const double sg = (g5 && h + k >= 6) ? -1.0 : 1.0;
+        const auto t = tile[s][k];
+        canon[(size_t)sh.pair[wave][s] * 12 + h + k] = make_double2(sg * (double)t.r, sg * (double)t.i);
+      }
+    }
+  }
+}
+
+// A site a lane all the same for one FP64 right-hand side: there the pieces
+// make up whole lines while they are in L2, and the LDS costs wavefronts (D_r
+// at 24^3x64: 485 us, through LDS 498).
+template <typename S>
+__device__ __forceinline__ void store_canon_direct(double2* canon, int lex, bool g5, bool zero,
+                                                   const cpx<typename Compute<S>::T> v[12]) {
+  double2* site = canon + (size_t)lex * 12;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const double sg = (g5 && k >= 6) ? -1.0 : 1.0;
+    site[k] = make_double2(sg * (double)v[k].r, sg * (double)v[k].i);
+  }
+  if (zero) {
+    double2* other = canon + (size_t)(lex ^ 1) * 12;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) other[k] = make_double2(0.0, 0.0);
+  }
+}
+
 // S: spinor storage, G: link and clover storage (G = S, or FP16 fields with
-// FP32 spinors); lb: the lattice's logical block
+// FP32 spinors); lb: the lattice's logical block; p: output parity
 // RED (DIAG = 1, one right-hand side): also add <out, x> and ||out||^2 of the
 // site, in FP64 from the stored values, to red[0..3)
-// g0: first right-hand side of the thread's group (-1: blockIdx.y * NR)
+// CANON: out (and x of DIAG = 1) in the canonical layout
+// g0: first right-hand side of the thread's NR
 template <typename S, typename G, int DIAG, bool POSTINV, int NR, bool STREAM = false, bool RED = false,
-          bool PIN = true>
-__device__ __forceinline__ void dslash_site(const DslashArgs& a, int lb, double* red = nullptr, int g0 = -1) {
+          bool PIN = true, bool CANON = false, bool DIRECT = false>
+__device__ __forceinline__ void dslash_site(const DslashArgs& a, int lb, int p, int g0, double* red = nullptr) {
   using C = typename Compute<S>::T;
-  const int i = lb * blockDim.x + threadIdx.x;
-  if (lb >= a.nblocks || i >= a.g.Vh) return;
-  if (g0 < 0) g0 = blockIdx.y * NR;
+  int i = lb * blockDim.x + threadIdx.x;
+  if (lb >= a.nblocks) return;
+  // sites of this wavefront (canonical output: lanes beyond the last site stay and repeat it)
+  const int count = min(64, a.g.Vh - (i & ~63));
+  if constexpr (CANON && !DIRECT) {
+    if (count <= 0) return;
+    i = min(i, a.g.Vh - 1);
+  } else {
+    if (i >= a.g.Vh) return;
+  }
+  if (a.tile_z > 0) i = tile_site(a, i);
   const int nr = min(NR, a.nrhs - g0);
-  const int p = a.parity;
+  __shared__ typename std::conditional<CANON && !DIRECT, CanonTile<S>, int>::type tile;
+  (void)tile;
+  // both parities in one launch: the second set of pointers is the odd output's
+  const void* in = p != a.parity ? a.in2 : a.in;
+  const void* xin = p != a.parity ? a.x2 : a.x;
+  void* outp = p != a.parity ? a.out2 : a.out;
   int c[4];
   cb_coords(a.g, i, p, c);
 
@@ -239,10 +349,11 @@ __device__ __forceinline__ void dslash_site(const DslashArgs& a, int lb, double*
   for (int r = 0; r < NR; ++r)
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[r][k] = mk((C)0, (C)0);
-  hop_mu<S, G, 0, NR, STREAM, PIN>(a, p, i, c, g0, nr, acc);
-  hop_mu<S, G, 1, NR, STREAM, PIN>(a, p, i, c, g0, nr, acc);
-  hop_mu<S, G, 2, NR, STREAM, PIN>(a, p, i, c, g0, nr, acc);
-  hop_mu<S, G, 3, NR, STREAM, PIN>(a, p, i, c, g0, nr, acc);
+  hop_mu<S, G, 0, NR, STREAM, PIN>(a, in, p, i, c, g0, nr, acc);
+  hop_mu<S, G, 1, NR, STREAM, PIN>(a, in, p, i, c, g0, nr, acc);
+  hop_mu<S, G, 2, NR, STREAM, PIN>(a, in, p, i, c, g0, nr, acc);
+  hop_mu<S, G, 3, NR, STREAM, PIN>(a, in, p, i, c, g0, nr, acc);
+  const int lex = 2 * i + (c[0] & 1);
 
   const C f = (C)(-0.5 * a.coeff);
 #pragma unroll
@@ -263,7 +374,12 @@ __device__ __forceinline__ void dslash_site(const DslashArgs& a, int lb, double*
     cpx<C> xv[NR][12];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r < nr) SpinorIO<S>::template load<STREAM>(rhs_ptr<S>(a.x, a.rstride, g0 + r), a.g.Vh, i, xv[r]);
+      if (r < nr) {
+        if constexpr (CANON && DIAG == 1)
+          load_canon<S>(a.canon_x + (size_t)(g0 + r) * a.canon_stride + (size_t)lex * 12, a.g5_x, xv[r]);
+        else
+          SpinorIO<S>::template load<STREAM>(rhs_ptr<S>(xin, a.rstride, g0 + r), a.g.Vh, i, xv[r]);
+      }
     if constexpr (DIAG == 2) {
       cpx<C> ax[NR][12];
       clover_multi<G, C, NR, STREAM>(a.clov, a.g.Vh, p, 0, i, nr, xv, ax);
@@ -290,35 +406,71 @@ __device__ __forceinline__ void dslash_site(const DslashArgs& a, int lb, double*
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r)
-    if (r < nr)
-      SpinorIO<S>::template store<STREAM>(const_cast<void*>(rhs_ptr<S>(a.out, a.rstride, g0 + r)), a.g.Vh, i, out[r]);
+    if (r < nr) {
+      if constexpr (CANON && DIRECT)
+        store_canon_direct<S>(a.canon_out + (size_t)(g0 + r) * a.canon_stride, lex, a.g5_out, a.zero_other, out[r]);
+      else if constexpr (CANON)
+        store_canon<S>(tile, a.canon_out + (size_t)(g0 + r) * a.canon_stride, lex, count, a.g5_out, a.zero_other,
+                       out[r]);
+      else
+        SpinorIO<S>::template store<STREAM>(const_cast<void*>(rhs_ptr<S>(outp, a.rstride, g0 + r)), a.g.Vh, i, out[r]);
+    }
 }
 
-template <typename S, typename G, int DIAG, bool POSTINV, int NR, bool STREAM>
+// Logical workgroup L of a launch: site block L / np (and parity L mod np when
+// the launch covers both: the two parities of a block read the same links, so
+// they run side by side on one XCD).
+__device__ __forceinline__ int launch_parity(const DslashArgs& a, int& L) {
+  if (!a.both) return a.parity;
+  const int p = L & 1;
+  L >>= 1;
+  return p;
+}
+
+// one right-hand side per thread, right-hand side blockIdx.y
+template <typename S, typename G, int DIAG, bool POSTINV, bool STREAM, bool CANON>
 __global__ void __launch_bounds__(256) dslash_kernel(DslashArgs a) {
-  dslash_site<S, G, DIAG, POSTINV, NR, STREAM>(a, xcd_block(a.nblocks));
+  int L = xcd_block(a.nblocks << a.both);
+  const int p = launch_parity(a, L);
+  dslash_site<S, G, DIAG, POSTINV, 1, STREAM, false, true, CANON, sizeof(S) == 8>(a, L, p, blockIdx.y);
 }
 
-// Small lattices (a few workgroups per compute unit, so one or two wavefronts
-// per SIMD whatever the register count): the directions are not pinned, so
-// the compiler may issue the loads of all eight hops before their arithmetic
-// and more of the gather is in flight at once.  Same arithmetic, same order,
-// same bits as dslash_kernel.
-template <typename S, typename G, int DIAG, bool POSTINV, bool STREAM>
+// NR right-hand sides per thread, a site block's in consecutive workgroups:
+// they land on one XCD (xcd_block) and run close together, so the first to
+// read a link or clover record brings it into that XCD's L2.
+template <typename S, typename G, int DIAG, bool POSTINV, int NR, bool PIN, bool CANON>
+__device__ __forceinline__ void dslash_interleaved(const DslashArgs& a) {
+  const int groups = (a.nrhs + NR - 1) / NR;
+  const int M = xcd_block((a.nblocks * groups) << a.both);
+  int L = M / groups;
+  const int g0 = NR * (M - L * groups);
+  const int p = launch_parity(a, L);
+  dslash_site<S, G, DIAG, POSTINV, NR, false, false, PIN, CANON>(a, L, p, g0);
+}
+
+// Small grids (a few workgroups per compute unit, so one or two wavefronts per
+// SIMD whatever the register count): the directions are not pinned, so the
+// compiler may issue the loads of all eight hops before their arithmetic and
+// more of the gather is in flight at once.  Same arithmetic, same order, same
+// bits as dslash_kernel.
+template <typename S, typename G, int DIAG, bool POSTINV, bool CANON>
 __global__ void __launch_bounds__(256) dslash_kernel_wide(DslashArgs a) {
-  dslash_site<S, G, DIAG, POSTINV, 1, STREAM, false, false>(a, xcd_block(a.nblocks));
+  dslash_interleaved<S, G, DIAG, POSTINV, 1, false, CANON>(a);
 }
 
-// Several right-hand sides, one per thread: logical workgroup L handles site
-// block L / nrhs of right-hand side L % nrhs, so the nrhs workgroups of a site
-// block are consecutive, land on one XCD (xcd_block) and run close together:
-// the first to read a link or clover record brings it into that XCD's L2 and
-// the others find it there, while every thread keeps the register budget of
-// the single-right-hand-side kernel.
-template <typename S, typename G, int DIAG, bool POSTINV, bool STREAM>
+// Several right-hand sides.  The gathers bound large batches: with one
+// right-hand side per thread each launch moved 3.9 GB beyond L2 where 1.3 GB
+// are compulsory (FP32, 12 right-hand sides, 24^3x64).  Two halve the reads of
+// the shared records, and the sites are visited in tiles of z and t
+// (tile_site) so that a spinor's neighbours run while it is in L2.  24^3x64,
+// 12 right-hand sides, us, the odd hop with the clover inverse / the even hop
+// with A x: FP64 1325 / 1404 in lattice order and one per thread, 1255 / 1292
+// two per thread, 1138 / 1136 with 4x8 tiles; FP32 681 / 741, 606 / 671, 572 /
+// 605.  Three per thread are faster for one of the two FP64 forms only (1015 /
+// 1152), four are slower (registers).  Same bits.
+template <typename S, typename G, int DIAG, bool POSTINV, int NR, bool CANON>
 __global__ void __launch_bounds__(256) dslash_kernel_rhs(DslashArgs a) {
-  const int L = xcd_block(a.nblocks * a.nrhs);
-  dslash_site<S, G, DIAG, POSTINV, 1, STREAM>(a, L / a.nrhs, nullptr, L % a.nrhs);
+  dslash_interleaved<S, G, DIAG, POSTINV, NR, true, CANON>(a);
 }
 
 // The DIAG = 1 hop of D_r with the minimal-residual sums of the smoother
@@ -328,7 +480,7 @@ __global__ void __launch_bounds__(256) dslash_kernel_rhs(DslashArgs a) {
 template <typename S, typename G, bool STREAM, bool PIN = true>
 __global__ void __launch_bounds__(256) dslash_red_kernel(DslashArgs a, RedOut o) {
   double v[3] = {0.0, 0.0, 0.0};
-  dslash_site<S, G, 1, false, 1, STREAM, true, PIN>(a, xcd_block(a.nblocks), v);
+  dslash_site<S, G, 1, false, 1, STREAM, true, PIN>(a, xcd_block(a.nblocks), a.parity, 0, v);
   blas_detail::block_reduce<3>(v, o);
 }
 
@@ -338,43 +490,60 @@ template <typename S, typename G, int DIAG, bool POSTINV>
 __global__ void __launch_bounds__(256) dslash_multi_kernel(DslashMulti m) {
   int l = 0;
   while (l + 1 < m.nl && (int)blockIdx.x >= m.off[l + 1]) ++l;
-  dslash_site<S, G, DIAG, POSTINV, 1>(m.a[l], (int)blockIdx.x - m.off[l]);
+  dslash_site<S, G, DIAG, POSTINV, 1>(m.a[l], (int)blockIdx.x - m.off[l], m.a[l].parity, 0);
 }
 
-// out_p = A_p^(kind) in_p   (site-local clover or clover inverse), NR right-hand sides per thread
-template <typename S, typename G, int NR>
-__global__ void __launch_bounds__(256) clover_kernel(void* out, const void* in, const void* clov, int Vh, int p,
-                                                     int kind, int nrhs, size_t rstride) {
+// out_p = A_p^(kind) in_p (site-local clover or clover inverse), one
+// right-hand side per thread; both parities in one launch when a.both.  The
+// workgroups of a site block's right-hand sides are consecutive (as
+// dslash_kernel_rhs): the records they share are read once from HBM and then
+// from L2.  CIN, COUT: the input (with gamma5 in front if g5) or the output in
+// the canonical layout.
+template <typename S, typename G, bool CIN, bool COUT>
+__global__ void __launch_bounds__(256) clover_kernel(CloverArgs a) {
   using C = typename Compute<S>::T;
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= Vh) return;
-  const int g0 = blockIdx.y * NR;
-  const int nr = min(NR, nrhs - g0);
-  cpx<C> v[NR][12], o[NR][12];
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-    if (r < nr) SpinorIO<S>::load(rhs_ptr<S>(in, rstride, g0 + r), Vh, i, v[r]);
-  clover_multi<G, C, NR>(clov, Vh, p, kind, i, nr, v, o);
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-    if (r < nr) SpinorIO<S>::store(const_cast<void*>(rhs_ptr<S>(out, rstride, g0 + r)), Vh, i, o[r]);
-}
-
-// Several right-hand sides, one per thread, in interleaved workgroups (as
-// dslash_kernel_rhs): the nrhs workgroups of a site block are consecutive, so
-// the clover records they share are read once from HBM and then from L2.
-template <typename S, typename G>
-__global__ void __launch_bounds__(256) clover_kernel_rhs(void* out, const void* in, const void* clov, int Vh, int p,
-                                                         int kind, int nrhs, size_t rstride, int nblocks) {
-  using C = typename Compute<S>::T;
-  const int L = xcd_block(nblocks * nrhs);
-  const int lb = L / nrhs, r = L - lb * nrhs;
-  const int i = lb * blockDim.x + threadIdx.x;
-  if (lb >= nblocks || i >= Vh) return;
+  int L = xcd_block((a.nblocks * a.nrhs) << a.both);
+  int lb = L / a.nrhs;
+  const int r = L - lb * a.nrhs;
+  int p = a.parity;
+  if (a.both) {
+    p = lb & 1;
+    lb >>= 1;
+  }
+  int i = lb * blockDim.x + threadIdx.x;
+  if (lb >= a.nblocks) return;
+  const int count = min(64, a.Vh - (i & ~63));
+  __shared__ typename std::conditional<COUT, CanonTile<S>, int>::type tile;
+  (void)tile;
+  if constexpr (COUT) {
+    if (count <= 0) return;
+    i = min(i, a.Vh - 1);
+  } else {
+    if (i >= a.Vh) return;
+  }
+  const void* in = p != a.parity ? a.in2 : a.in;
+  void* out = p != a.parity ? a.out2 : a.out;
+  int lex = 0;
+  if constexpr (CIN || COUT) {
+    int c[4];
+    cb_coords(a.g, i, p, c);
+    lex = 2 * i + (c[0] & 1);
+  }
   cpx<C> v[1][12], o[1][12];
-  SpinorIO<S>::load(rhs_ptr<S>(in, rstride, r), Vh, i, v[0]);
-  clover_multi<G, C, 1>(clov, Vh, p, kind, i, 1, v, o);
-  SpinorIO<S>::store(const_cast<void*>(rhs_ptr<S>(out, rstride, r)), Vh, i, o[0]);
+  if constexpr (CIN) {
+    load_canon<S>(a.canon_in + (size_t)r * a.canon_stride + (size_t)lex * 12, a.g5, v[0]);
+  } else {
+    SpinorIO<S>::load(rhs_ptr<S>(in, a.rstride, r), a.Vh, i, v[0]);
+    if (a.g5) {
+#pragma unroll
+      for (int k = 6; k < 12; ++k) v[0][k] = mk(-v[0][k].r, -v[0][k].i);
+    }
+  }
+  clover_multi<G, C, 1>(a.clov, a.Vh, p, a.kind, i, 1, v, o);
+  if constexpr (COUT)
+    store_canon<S>(tile, a.canon_out + (size_t)r * a.canon_stride, lex, count, false, false, o[0]);
+  else
+    SpinorIO<S>::store(const_cast<void*>(rhs_ptr<S>(out, a.rstride, r)), a.Vh, i, o[0]);
 }
 
 // The smoother's minimal-residual update of the previous step fused into the
@@ -423,12 +592,6 @@ bool launch_clover_mr(int prec, void* out, void* r, void* e, const void* Ar, con
   return true;
 }
 
-// right-hand sides per thread: FP64 keeps at most 2 in registers, FP32/FP16 4
-template <typename S>
-constexpr int max_group() {
-  return sizeof(S) == 8 ? 2 : 4;
-}
-
 // compute units of the current device (queried once)
 static int device_cus() {
   static int cus = 0;
@@ -441,92 +604,79 @@ static int device_cus() {
   return cus;
 }
 
-// a single-right-hand-side grid of at most two 256-thread workgroups per compute unit
-static bool small_grid(const DslashArgs& a) { return a.nrhs == 1 && (a.g.Vh + 255) / 256 <= 2 * device_cus(); }
-
-template <typename S, typename G, int NR>
-static void launch_dslash_nr(int diag, bool postinv, DslashArgs a, hipStream_t st) {
-  const int threads = a.threads > 0 ? a.threads : 256;
-  if (threads != 64 && threads != 128 && threads != 256) fail(WCMG_EINVAL, "unsupported Dslash block size");
-  a.nblocks = (a.g.Vh + threads - 1) / threads;
-  dim3 grid(xcd_grid(a.nblocks), (a.nrhs + NR - 1) / NR);
-  if constexpr (NR == 1) {
-    if (small_grid(a)) {
-      const bool stream = a.stream > 0;
-#define WCMG_DW(D, P)                                                                               \
-  do {                                                                                            \
-    if (stream)                                                                                   \
-      hipLaunchKernelGGL((dslash_kernel_wide<S, G, D, P, true>), grid, dim3(threads), 0, st, a);  \
-    else                                                                                          \
-      hipLaunchKernelGGL((dslash_kernel_wide<S, G, D, P, false>), grid, dim3(threads), 0, st, a); \
-  } while (0)
-      if (diag == 0 && !postinv) WCMG_DW(0, false);
-      else if (diag == 0 && postinv) WCMG_DW(0, true);
-      else if (diag == 1 && !postinv) WCMG_DW(1, false);
-      else if (diag == 1 && postinv) WCMG_DW(1, true);
-      else if (diag == 2 && !postinv) WCMG_DW(2, false);
-      else WCMG_DW(2, true);
-#undef WCMG_DW
-      HIPCHK(hipGetLastError());
-      return;
-    }
-  }
-  // stream the fields and the output past the caches when the fields (links and both
-  // clover records, both parities) exceed three quarters of the 256 MB Infinity Cache
-  const bool stream = a.stream >= 0 ? a.stream != 0 : (double)a.g.Vh * 432.0 * sizeof(G) > 192.0e6;
-#define WCMG_DS(D, P)                                                                                  \
-  do {                                                                                               \
-    if (stream)                                                                                      \
-      hipLaunchKernelGGL((dslash_kernel<S, G, D, P, NR, true>), grid, dim3(threads), 0, st, a);    \
-    else                                                                                             \
-      hipLaunchKernelGGL((dslash_kernel<S, G, D, P, NR, false>), grid, dim3(threads), 0, st, a);   \
-  } while (0)
-  if (diag == 0 && !postinv) WCMG_DS(0, false);
-  else if (diag == 0 && postinv) WCMG_DS(0, true);
-  else if (diag == 1 && !postinv) WCMG_DS(1, false);
-  else if (diag == 1 && postinv) WCMG_DS(1, true);
-  else if (diag == 2 && !postinv) WCMG_DS(2, false);
-  else WCMG_DS(2, true);
-#undef WCMG_DS
-  HIPCHK(hipGetLastError());
+// a grid of at most two 256-thread workgroups per compute unit with one right-hand side per thread
+static bool small_grid(const DslashArgs& a) {
+  return ((long)((a.g.Vh + 255) / 256) * a.nrhs) << a.both <= 2 * device_cus();
+}
+// Two right-hand sides per thread from 12 workgroups per compute unit on: with
+// 12 right-hand sides they are faster in every form at 16^3x64 (12 per unit;
+// FP32 odd hop 173 us) and beyond, and lose at 16^3x32 (6 per unit; FP32 93
+// against 90 us, 108 against 86), where half the wavefronts hide less.
+static bool large_batch(const DslashArgs& a) {
+  return ((long)((a.g.Vh + 255) / 256) * ((a.nrhs + 1) / 2)) << a.both >= 12 * device_cus();
 }
 
-template <typename S, typename G>
-static void launch_dslash_rhs(int diag, bool postinv, DslashArgs a, hipStream_t st) {
-  const int threads = a.threads > 0 ? a.threads : 256;
+// stream the fields and the output past the caches when the fields (links and both
+// clover records, both parities) exceed three quarters of the 256 MB Infinity Cache
+template <typename G>
+static bool stream_fields(const DslashArgs& a) {
+  return (double)a.g.Vh * 432.0 * sizeof(G) > 192.0e6;
+}
+
+// largest divisor of n that is at most m
+static int divisor(int n, int m) {
+  while (n % m) --m;
+  return m;
+}
+
+template <typename S, typename G, int D, bool P, bool CANON>
+static void launch_variant(DslashArgs a, hipStream_t st) {
+  // a grid that leaves most compute units idle is spread over four times as many in small workgroups
+  const bool few = ((long)((a.g.Vh + 255) / 256) * a.nrhs) << a.both <= device_cus() / 4;
+  const int threads = a.threads > 0 ? a.threads : (few ? 64 : 256);
   if (threads != 64 && threads != 128 && threads != 256) fail(WCMG_EINVAL, "unsupported Dslash block size");
   a.nblocks = (a.g.Vh + threads - 1) / threads;
-  if ((long)a.nblocks * a.nrhs > (1L << 30)) fail(WCMG_EINVAL, "too many workgroups");
-  const dim3 grid(xcd_grid(a.nblocks * a.nrhs));
-  // the right-hand sides of a site block reuse its links and clover records
-  // from L2, so the fields are not streamed past the caches unless asked for
-  const bool stream = a.stream > 0;
-#define WCMG_DR(D, P)                                                                                 \
-  do {                                                                                              \
-    if (stream)                                                                                     \
-      hipLaunchKernelGGL((dslash_kernel_rhs<S, G, D, P, true>), grid, dim3(threads), 0, st, a);     \
-    else                                                                                            \
-      hipLaunchKernelGGL((dslash_kernel_rhs<S, G, D, P, false>), grid, dim3(threads), 0, st, a);    \
-  } while (0)
-  if (diag == 0 && !postinv) WCMG_DR(0, false);
-  else if (diag == 0 && postinv) WCMG_DR(0, true);
-  else if (diag == 1 && !postinv) WCMG_DR(1, false);
-  else if (diag == 1 && postinv) WCMG_DR(1, true);
-  else if (diag == 2 && !postinv) WCMG_DR(2, false);
-  else WCMG_DR(2, true);
-#undef WCMG_DR
+  if ((long)a.nblocks * a.nrhs > (1L << 29)) fail(WCMG_EINVAL, "too many workgroups");
+  auto grid_of = [&](int nr) { return dim3(xcd_grid((a.nblocks * ((a.nrhs + nr - 1) / nr)) << a.both)); };
+  // F16 spinors with A^-1 and x: the compiler contracts the sum differently for two
+  // right-hand sides, and the last bits would depend on the batch
+  constexpr bool two = !(sizeof(S) == 2 && D == 1 && P);
+  if (two && a.nrhs > 1 && (a.group == -2 || (a.group == 0 && large_batch(a)))) {
+    // tiles of 4 x 8 planes measured best of 2..8 x 2..8 at 24^3x64 in both precisions
+    a.tile_z = divisor(a.g.L[2], 4);
+    a.tile_t = divisor(a.g.L[3], 8);
+    hipLaunchKernelGGL((dslash_kernel_rhs<S, G, D, P, 2, CANON>), grid_of(2), dim3(threads), 0, st, a);
+  } else if (small_grid(a)) {
+    hipLaunchKernelGGL((dslash_kernel_wide<S, G, D, P, CANON>), grid_of(1), dim3(threads), 0, st, a);
+  } else if (a.nrhs > 1 && a.group != 1) {
+    hipLaunchKernelGGL((dslash_kernel_rhs<S, G, D, P, 1, CANON>), grid_of(1), dim3(threads), 0, st, a);
+  } else {
+    const dim3 grid(xcd_grid(a.nblocks << a.both), a.nrhs);
+    if (stream_fields<G>(a))
+      hipLaunchKernelGGL((dslash_kernel<S, G, D, P, true, CANON>), grid, dim3(threads), 0, st, a);
+    else
+      hipLaunchKernelGGL((dslash_kernel<S, G, D, P, false, CANON>), grid, dim3(threads), 0, st, a);
+  }
   HIPCHK(hipGetLastError());
 }
 
 template <typename S, typename G>
 static void launch_dslash_t(int diag, bool postinv, const DslashArgs& a, hipStream_t st) {
-  // several right-hand sides: one per thread, interleaved workgroups, unless a group size is asked for
-  if (a.nrhs > 1 && (a.group == 0 || a.group == -1)) return launch_dslash_rhs<S, G>(diag, postinv, a, st);
-  int g = a.nrhs >= max_group<S>() ? max_group<S>() : (a.nrhs >= 2 ? 2 : 1);
-  if (a.group > 0) g = std::min(a.group, max_group<S>());
-  if (g == 1) launch_dslash_nr<S, G, 1>(diag, postinv, a, st);
-  else if (g == 2) launch_dslash_nr<S, G, 2>(diag, postinv, a, st);
-  else launch_dslash_nr<S, G, max_group<S>()>(diag, postinv, a, st);
+  // the canonical output belongs to the operator applies: the last hop of each form
+  if constexpr (std::is_same<S, G>::value) {
+    if (a.canon_out) {
+      if (diag == 1 && !postinv) return launch_variant<S, G, 1, false, true>(a, st);
+      if (diag == 1 && postinv) return launch_variant<S, G, 1, true, true>(a, st);
+      if (diag == 2 && !postinv) return launch_variant<S, G, 2, false, true>(a, st);
+    }
+  }
+  if (a.canon_out) fail(WCMG_EINVAL, "no canonical output in this form of the hop");
+  if (diag == 0 && !postinv) launch_variant<S, G, 0, false, false>(a, st);
+  else if (diag == 0) launch_variant<S, G, 0, true, false>(a, st);
+  else if (diag == 1 && !postinv) launch_variant<S, G, 1, false, false>(a, st);
+  else if (diag == 1) launch_variant<S, G, 1, true, false>(a, st);
+  else if (!postinv) launch_variant<S, G, 2, false, false>(a, st);
+  else launch_variant<S, G, 2, true, false>(a, st);
 }
 
 void launch_dslash(int prec, int diag, bool postinv, const DslashArgs& a, hipStream_t st) {
@@ -541,14 +691,10 @@ void launch_dslash(int prec, int diag, bool postinv, const DslashArgs& a, hipStr
 
 template <typename S, typename G>
 static void launch_dslash_red_t(DslashArgs a, const RedOut& o, hipStream_t st) {
-  const bool stream = a.stream >= 0 ? a.stream != 0 : (double)a.g.Vh * 432.0 * sizeof(G) > 192.0e6;
   dim3 grid(xcd_grid(a.nblocks));
   if (small_grid(a)) {
-    if (stream)
-      hipLaunchKernelGGL((dslash_red_kernel<S, G, true, false>), grid, dim3(256), 0, st, a, o);
-    else
-      hipLaunchKernelGGL((dslash_red_kernel<S, G, false, false>), grid, dim3(256), 0, st, a, o);
-  } else if (stream) {
+    hipLaunchKernelGGL((dslash_red_kernel<S, G, false, false>), grid, dim3(256), 0, st, a, o);
+  } else if (stream_fields<G>(a)) {
     hipLaunchKernelGGL((dslash_red_kernel<S, G, true>), grid, dim3(256), 0, st, a, o);
   } else {
     hipLaunchKernelGGL((dslash_red_kernel<S, G, false>), grid, dim3(256), 0, st, a, o);
@@ -572,35 +718,31 @@ bool launch_dslash_red(int prec, const DslashArgs& a0, const RedOut& o, hipStrea
   return true;
 }
 
-template <typename S, typename G, int NR>
-static void launch_clover_nr(void* out, const void* in, const void* clov, int Vh, int p, int kind, int nrhs,
-                             size_t rstride, hipStream_t st) {
-  dim3 grid((Vh + 255) / 256, (nrhs + NR - 1) / NR);
-  hipLaunchKernelGGL((clover_kernel<S, G, NR>), grid, dim3(256), 0, st, out, in, clov, Vh, p, kind, nrhs, rstride);
-}
-
 template <typename S, typename G>
-static void launch_clover_t(void* out, const void* in, const void* clov, int Vh, int p, int kind, int nrhs,
-                            size_t rstride, hipStream_t st) {
-  if (nrhs > 1) {
-    const int nb = (Vh + 255) / 256;
-    hipLaunchKernelGGL((clover_kernel_rhs<S, G>), dim3(xcd_grid(nb * nrhs)), dim3(256), 0, st, out, in, clov, Vh, p,
-                       kind, nrhs, rstride, nb);
-    return;
+static void launch_clover_t(CloverArgs a, hipStream_t st) {
+  a.nblocks = (a.Vh + 255) / 256;
+  const dim3 grid(xcd_grid((a.nblocks * a.nrhs) << a.both));
+  if constexpr (std::is_same<S, G>::value) {
+    if (a.canon_in) {
+      hipLaunchKernelGGL((clover_kernel<S, G, true, false>), grid, dim3(256), 0, st, a);
+      return;
+    }
+    if (a.canon_out) {
+      hipLaunchKernelGGL((clover_kernel<S, G, false, true>), grid, dim3(256), 0, st, a);
+      return;
+    }
   }
-  if (nrhs >= max_group<S>()) launch_clover_nr<S, G, max_group<S>()>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
-  else if (nrhs >= 2) launch_clover_nr<S, G, 2>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
-  else launch_clover_nr<S, G, 1>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
+  if (a.canon_in || a.canon_out) fail(WCMG_EINVAL, "canonical spinors with fields of another precision");
+  hipLaunchKernelGGL((clover_kernel<S, G, false, false>), grid, dim3(256), 0, st, a);
 }
 
-void launch_clover(int prec, void* out, const void* in, const void* clov, int Vh, int p, int kind, hipStream_t st,
-                   int nrhs, size_t rstride, int fprec) {
-  if (nrhs < 1) fail(WCMG_EINVAL, "nrhs must be >= 1");
+void launch_clover(int prec, const CloverArgs& a, int fprec, hipStream_t st) {
+  if (a.nrhs < 1) fail(WCMG_EINVAL, "nrhs must be >= 1");
   const int fp = fprec < 0 ? prec : fprec;
-  if (prec == WCMG_F64 && fp == WCMG_F64) launch_clover_t<double, double>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
-  else if (prec == WCMG_F32 && fp == WCMG_F32) launch_clover_t<float, float>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
-  else if (prec == WCMG_F32 && fp == WCMG_F16) launch_clover_t<float, __half>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
-  else if (prec == WCMG_F16 && fp == WCMG_F16) launch_clover_t<__half, __half>(out, in, clov, Vh, p, kind, nrhs, rstride, st);
+  if (prec == WCMG_F64 && fp == WCMG_F64) launch_clover_t<double, double>(a, st);
+  else if (prec == WCMG_F32 && fp == WCMG_F32) launch_clover_t<float, float>(a, st);
+  else if (prec == WCMG_F32 && fp == WCMG_F16) launch_clover_t<float, __half>(a, st);
+  else if (prec == WCMG_F16 && fp == WCMG_F16) launch_clover_t<__half, __half>(a, st);
   else fail(WCMG_EINVAL, "unsupported spinor / field precision pair");
   HIPCHK(hipGetLastError());
 }

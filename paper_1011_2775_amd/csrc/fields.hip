@@ -43,26 +43,35 @@ __global__ void k_gauge_to_internal(void* dst, const double2* canon, DGeom g, in
     }
 }
 
+// right-hand side blockIdx.y; odd == nullptr: one thread per even site, else one per site
 template <typename S>
-__global__ void k_spinor_to_internal(void* even, void* odd, const double2* canon, DGeom g, int V, int g5) {
+__global__ void k_spinor_to_internal(void* even, void* odd, const double2* canon, DGeom g, int V, int g5,
+                                     size_t half_bytes) {
   using C = typename Compute<S>::T;
-  int lex = blockIdx.x * blockDim.x + threadIdx.x;
-  if (lex >= V) return;
-  int c[4];
-  coords_of(g.L, lex, c);
-  int p = (c[0] + c[1] + c[2] + c[3]) & 1;
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (odd ? V : V / 2)) return;
+  int lex = t, c[4];
+  if (odd) {
+    coords_of(g.L, lex, c);
+  } else {
+    cb_coords(g, t, 0, c);
+    lex = 2 * t + (c[0] & 1);
+  }
+  const int p = (c[0] + c[1] + c[2] + c[3]) & 1;
+  canon += ((size_t)blockIdx.y * V + lex) * 12;
   cpx<C> v[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
-    double2 t = canon[(size_t)lex * 12 + k];
+    double2 u = canon[k];
     C sg = (g5 && k >= 6) ? (C)-1 : (C)1;
-    v[k] = mk((C)(sg * t.x), (C)(sg * t.y));
+    v[k] = mk((C)(sg * u.x), (C)(sg * u.y));
   }
-  SpinorIO<S>::store(p ? odd : even, g.Vh, lex >> 1, v);
+  SpinorIO<S>::store(reinterpret_cast<char*>(p ? odd : even) + blockIdx.y * half_bytes, g.Vh, lex >> 1, v);
 }
 
 template <typename S>
-__global__ void k_spinor_from_internal(double2* canon, const void* even, const void* odd, DGeom g, int V, int g5) {
+__global__ void k_spinor_from_internal(double2* canon, const void* even, const void* odd, DGeom g, int V, int g5,
+                                       size_t half_bytes) {
   using C = typename Compute<S>::T;
   int lex = blockIdx.x * blockDim.x + threadIdx.x;
   if (lex >= V) return;
@@ -72,7 +81,7 @@ __global__ void k_spinor_from_internal(double2* canon, const void* even, const v
   const void* src = p ? odd : even;
   cpx<C> v[12];
   if (src) {
-    SpinorIO<S>::load(src, g.Vh, lex >> 1, v);
+    SpinorIO<S>::load(reinterpret_cast<const char*>(src) + blockIdx.y * half_bytes, g.Vh, lex >> 1, v);
   } else {
 #pragma unroll
     for (int k = 0; k < 12; ++k) v[k] = mk((C)0, (C)0);
@@ -80,7 +89,7 @@ __global__ void k_spinor_from_internal(double2* canon, const void* even, const v
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
     double sg = (g5 && k >= 6) ? -1.0 : 1.0;
-    canon[(size_t)lex * 12 + k] = make_double2(sg * (double)v[k].r, sg * (double)v[k].i);
+    canon[((size_t)blockIdx.y * V + lex) * 12 + k] = make_double2(sg * (double)v[k].r, sg * (double)v[k].i);
   }
 }
 
@@ -336,32 +345,28 @@ void gauge_to_internal(int prec, void* dst, const void* canon, const Geom& g, hi
 }
 
 void spinor_to_internal(int prec, void* even, void* odd, const void* canon, const Geom& g, bool g5,
-                        hipStream_t st) {
-  DGeom d = dgeom(g);
+                        hipStream_t st, int nrhs) {
+  const dim3 grid(grid_for(odd ? g.V : g.Vh).x, nrhs);
+  const size_t hb = spinor_bytes(prec, g.Vh);
   auto c = reinterpret_cast<const double2*>(canon);
-  if (prec == WCMG_F64)
-    hipLaunchKernelGGL(k_spinor_to_internal<double>, grid_for(g.V), dim3(kT), 0, st, even, odd, c, d, g.V, (int)g5);
-  else if (prec == WCMG_F32)
-    hipLaunchKernelGGL(k_spinor_to_internal<float>, grid_for(g.V), dim3(kT), 0, st, even, odd, c, d, g.V, (int)g5);
-  else
-    hipLaunchKernelGGL(k_spinor_to_internal<__half>, grid_for(g.V), dim3(kT), 0, st, even, odd, c, d, g.V,
-                       (int)g5);
+#define TI(S) hipLaunchKernelGGL(k_spinor_to_internal<S>, grid, dim3(kT), 0, st, even, odd, c, dgeom(g), g.V, (int)g5, hb)
+  if (prec == WCMG_F64) TI(double);
+  else if (prec == WCMG_F32) TI(float);
+  else TI(__half);
+#undef TI
   HIPCHK(hipGetLastError());
 }
 
 void spinor_from_internal(int prec, void* canon, const void* even, const void* odd, const Geom& g, bool g5,
-                          hipStream_t st) {
-  DGeom d = dgeom(g);
+                          hipStream_t st, int nrhs) {
+  const dim3 grid(grid_for(g.V).x, nrhs);
+  const size_t hb = spinor_bytes(prec, g.Vh);
   auto c = reinterpret_cast<double2*>(canon);
-  if (prec == WCMG_F64)
-    hipLaunchKernelGGL(k_spinor_from_internal<double>, grid_for(g.V), dim3(kT), 0, st, c, even, odd, d, g.V,
-                       (int)g5);
-  else if (prec == WCMG_F32)
-    hipLaunchKernelGGL(k_spinor_from_internal<float>, grid_for(g.V), dim3(kT), 0, st, c, even, odd, d, g.V,
-                       (int)g5);
-  else
-    hipLaunchKernelGGL(k_spinor_from_internal<__half>, grid_for(g.V), dim3(kT), 0, st, c, even, odd, d, g.V,
-                       (int)g5);
+#define FI(S) hipLaunchKernelGGL(k_spinor_from_internal<S>, grid, dim3(kT), 0, st, c, even, odd, dgeom(g), g.V, (int)g5, hb)
+  if (prec == WCMG_F64) FI(double);
+  else if (prec == WCMG_F32) FI(float);
+  else FI(__half);
+#undef FI
   HIPCHK(hipGetLastError());
 }
 

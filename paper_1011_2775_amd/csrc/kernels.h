@@ -19,10 +19,22 @@ struct DslashArgs {
   int nrhs = 1;        // right-hand sides: out, in, x hold nrhs spinors
   size_t rstride = 0;  // bytes between consecutive right-hand sides
   int threads = 0;     // launch shape: threads per block (64, 128, 256; 0 = 256)
-  int group = 0;       // right-hand sides per thread (1, 2, 4; 0 = default); -1: one per thread, the
-                       // right-hand sides of a site block in consecutive workgroups (fields shared in L2)
+  int group = 0;       // several right-hand sides: 1 one per thread, each over the whole lattice; -1 one
+                       // per thread, a site block's in consecutive workgroups (fields shared in L2); -2
+                       // two per thread, so arranged, in tiles of the lattice; 0 by the size of the grid
   int fprec = -1;      // storage of gauge and clover (-1: as the spinors; F16 with F32 spinors)
-  int stream = -1;     // non-temporal field loads: 1 on, 0 off, -1 when the fields exceed the Infinity Cache
+  int both = 0;        // 1: both parities in one launch (parity 0 above, parity 1 here)
+  void* out2 = nullptr;
+  const void* in2 = nullptr;
+  const void* x2 = nullptr;
+  // operator applies: output (and x of DIAG 1) in the canonical layout, right-hand sides
+  // canon_stride complexes apart; g5: gamma5 on reading or writing; zero_other: zeros on
+  // the sites of the other parity
+  double2* canon_out = nullptr;
+  const double2* canon_x = nullptr;
+  size_t canon_stride = 0;
+  int g5_out = 0, g5_x = 0, zero_other = 0;
+  int tile_z = 0, tile_t = 0;  // filled by the launcher
 };
 void launch_dslash(int prec, int diag, bool postinv, const DslashArgs& a, hipStream_t st);
 struct RedOut;
@@ -51,19 +63,38 @@ struct CloverMulti {
   int off[kMaxMulti + 1];
 };
 void launch_clover_multi(int prec, CloverMulti m, hipStream_t st);
-// out_r = A^(kind) in_r for nrhs spinors rstride bytes apart
-void launch_clover(int prec, void* out, const void* in, const void* clov, int Vh, int p, int kind,
-                   hipStream_t st, int nrhs = 1, size_t rstride = 0, int fprec = -1);
+// out_r = A^(kind) in_r (kind 0: A, 1: A^-1) for nrhs spinors rstride bytes apart
+struct CloverArgs {
+  void* out = nullptr;
+  const void* in = nullptr;
+  const void* clov = nullptr;
+  DGeom g;
+  int Vh = 0;
+  int parity = 0;
+  int kind = 0;
+  int nrhs = 1;
+  size_t rstride = 0;
+  int both = 0;  // both parities in one launch, as in DslashArgs
+  void* out2 = nullptr;
+  const void* in2 = nullptr;
+  const double2* canon_in = nullptr;  // input or output in the canonical layout
+  double2* canon_out = nullptr;
+  size_t canon_stride = 0;
+  int g5 = 0;  // gamma5 on the input
+  int nblocks = 0;  // filled by the launcher
+};
+void launch_clover(int prec, const CloverArgs& a, int fprec, hipStream_t st);
 
 // ------------------------------------------------------------ fields
 // canonical complex128 gauge [V][4][3][3] (device) -> internal links
 void gauge_to_internal(int prec, void* dst, const void* canon, const Geom& g, hipStream_t st);
-// canonical complex128 spinor [V][12] (device) <-> two internal parity halves
+// canonical complex128 spinors [nrhs][V][12] (device) <-> two internal parity halves
+// (nrhs of each, stored back to back); odd == nullptr skips the odd sites
 void spinor_to_internal(int prec, void* even, void* odd, const void* canon, const Geom& g, bool g5,
-                        hipStream_t st);
+                        hipStream_t st, int nrhs = 1);
 // odd == nullptr writes zeros on odd sites; even == nullptr writes zeros on even sites
 void spinor_from_internal(int prec, void* canon, const void* even, const void* odd, const Geom& g, bool g5,
-                          hipStream_t st);
+                          hipStream_t st, int nrhs = 1);
 // one parity, any precision pair
 void spinor_convert(int prec_dst, void* dst, int prec_src, const void* src, int Vh, hipStream_t st);
 void spinor_gamma5(int prec, void* v, int Vh, hipStream_t st);
@@ -91,9 +122,9 @@ void clover_relayout(int prec, void* dst, const double* src, int Vh, hipStream_t
 // per-block partials summed in block order by the last block to arrive).
 constexpr int kRedBlocks = 512;
 constexpr int kRedPartials = kRedBlocks * 128;
-// arrival counters of a sum: nine, a cache line apart, padded to a row; kRedRows sums at once
+// arrival counters of a sum: nine, a cache line apart; kRedRows sums at once
 constexpr int kCounterLine = 32;
-constexpr int kCounterRow = 16 * kCounterLine;
+constexpr int kCounterRow = 9 * kCounterLine;
 constexpr int kRedRows = 160;
 struct RedOut {
   double* res;        // device result

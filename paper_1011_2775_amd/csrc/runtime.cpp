@@ -122,14 +122,16 @@ KernelTimer::~KernelTimer() {
 // ------------------------------------------------------------------ reducer
 void Reducer::init(hipStream_t s) {
   st = s;
-  partial.alloc((size_t)kRedPartials * sizeof(double));
-  res.alloc(256 * sizeof(double));
-  counter.alloc((size_t)kRedRows * kCounterRow * sizeof(unsigned));
-  HIPCHK(hipMemset(counter.p, 0, (size_t)kRedRows * kCounterRow * sizeof(unsigned)));
+  const size_t nb = (size_t)kMaxBatch * kRedBlocks * 32, nc = (size_t)kRedRows * kCounterRow * sizeof(unsigned);
+  mem.alloc((kRedPartials + nb + 256) * sizeof(double) + nc);
+  partial = mem.as<double>();
+  part_b = partial + kRedPartials;
+  res = part_b + nb;
+  counter = reinterpret_cast<unsigned*>(res + 256);
+  HIPCHK(hipMemset(counter, 0, nc));
   HIPCHK(hipHostMalloc((void**)&host, 256 * sizeof(double), hipHostMallocDefault));
   HIPCHK(hipHostMalloc((void**)&host2, 16 * sizeof(double), hipHostMallocDefault));
   for (auto& e : ev2) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  part_b.alloc((size_t)kMaxBatch * kRedBlocks * 32 * sizeof(double));
 }
 const double* Reducer::fetch_rows(const double* dev, size_t pitch, int width, int rows) {
   if (width * rows > 256) fail(WCMG_EINVAL, "too many scalars for the host staging buffer");
@@ -184,23 +186,52 @@ void FineWork::ensure(int p, const Geom& g, int nrhs) {
   t3.alloc(b);
 }
 
-void FineOp::hop(void* out, const void* in, const void* x, int parity, int diag, bool postinv, double coeff,
-                 int nrhs) {
+DslashArgs FineOp::hop_args(double coeff, int nrhs) const {
   DslashArgs a;
-  a.out = out;
-  a.in = in;
-  a.x = x;
+  a.out = nullptr;
+  a.in = nullptr;
+  a.x = nullptr;
   a.gauge = F->gauge[fp()].p;
   a.clov = F->clov[fp()].p;
   a.fprec = fp();
   a.g = dgeom(F->g);
-  a.parity = parity;
+  a.parity = 0;
   a.nblocks = 0;
   a.coeff = coeff;
   a.nrhs = nrhs;
   a.rstride = hb();
+  return a;
+}
+
+void FineOp::hop(void* out, const void* in, const void* x, int parity, int diag, bool postinv, double coeff,
+                 int nrhs) {
+  DslashArgs a = hop_args(coeff, nrhs);
+  a.out = out;
+  a.in = in;
+  a.x = x;
+  a.parity = parity;
+  run_hop(a, diag, postinv);
+}
+
+void FineOp::hop_both(void* oe, void* oo, const void* ie, const void* io, const void* xe, const void* xo, int diag,
+                      int nrhs) {
+  DslashArgs a = hop_args(1.0, nrhs);
+  a.both = 1;
+  a.out = oe;
+  a.in = io;
+  a.x = xe;
+  a.out2 = oo;
+  a.in2 = ie;
+  a.x2 = xo;
+  run_hop(a, diag, false);
+}
+
+void FineOp::run_hop(DslashArgs& a, int diag, bool postinv) {
+  const int nrhs = a.nrhs;
   if (ctx->tuner.on) {
-    const std::array<int, 5> key{prec * 3 + fp(), diag, postinv ? 1 : 0, F->g.Vh, nrhs};
+    // launches over both parities and canonical outputs are variants of their own
+    const int form = a.both + (a.canon_out ? 2 : 0);
+    const std::array<int, 6> key{prec * 3 + fp(), diag, postinv ? 1 : 0, F->g.Vh, nrhs, form};
     auto it = ctx->tuner.best.find(key);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     HIPCHK(hipStreamIsCapturing(st, &cs));
@@ -210,10 +241,9 @@ void FineOp::hop(void* out, const void* in, const void* x, int parity, int diag,
       hipEvent_t e0, e1;
       HIPCHK(hipEventCreate(&e0));
       HIPCHK(hipEventCreate(&e1));
-      const int max_g = prec == WCMG_F64 ? 2 : 4;
       for (int threads : {64, 128, 256})
-        for (int group : {-1, 1, 2, 4}) {
-          if (group > max_g || (group > 1 && group > nrhs) || (group < 0 && nrhs == 1)) continue;
+        for (int group : {-2, -1, 1}) {
+          if (group < 0 && nrhs == 1) continue;
           DslashArgs t = a;
           t.threads = threads;
           t.group = group;
@@ -246,14 +276,43 @@ void FineOp::hop(void* out, const void* in, const void* x, int parity, int diag,
   if (e) ctx->timer.end(id, e);
 }
 
-void FineOp::clover(void* out, const void* in, int parity, int kind, int nrhs) {
+CloverArgs FineOp::clover_args(int kind, int nrhs) const {
+  CloverArgs a;
+  a.clov = F->clov[fp()].p;
+  a.g = dgeom(F->g);
+  a.Vh = F->g.Vh;
+  a.kind = kind;
+  a.nrhs = nrhs;
+  a.rstride = hb();
+  return a;
+}
+
+void FineOp::run_clover(const CloverArgs& a) {
   // timer ids: one right-hand side 64 + precision, batches 67 + precision, FP16 fields
   // with FP32 spinors 70
-  const int id = fp() != prec ? 70 : (nrhs > 1 ? 67 : 64) + prec;
+  const int id = fp() != prec ? 70 : (a.nrhs > 1 ? 67 : 64) + prec;
   hipEvent_t e = nullptr;
   if (ctx->timer.on) ctx->timer.begin(id, &e);
-  launch_clover(prec, out, in, F->clov[fp()].p, F->g.Vh, parity, kind, st, nrhs, hb(), fp());
+  launch_clover(prec, a, fp(), st);
   if (e) ctx->timer.end(id, e);
+}
+
+void FineOp::clover(void* out, const void* in, int parity, int kind, int nrhs) {
+  CloverArgs a = clover_args(kind, nrhs);
+  a.out = out;
+  a.in = in;
+  a.parity = parity;
+  run_clover(a);
+}
+
+void FineOp::clover_both(void* oe, void* oo, const void* ie, const void* io, int kind, int nrhs) {
+  CloverArgs a = clover_args(kind, nrhs);
+  a.both = 1;
+  a.out = oe;
+  a.in = ie;
+  a.out2 = oo;
+  a.in2 = io;
+  run_clover(a);
 }
 
 void FineOp::Dr(void* out, const void* y, int nrhs) {
@@ -321,16 +380,107 @@ void FineOp::Dr_dag(void* out, const void* y, int nrhs) {
 }
 
 void FineOp::D(void* oe, void* oo, const void* ie, const void* io, int nrhs) {
-  hop(oe, io, ie, 0, 2, false, 1.0, nrhs);
-  hop(oo, ie, io, 1, 2, false, 1.0, nrhs);
+  hop_both(oe, oo, ie, io, ie, io, 2, nrhs);
 }
 
 void FineOp::Dp(void* oe, void* oo, const void* ie, const void* io, int nrhs) {
   w->ensure(prec, F->g, nrhs);
-  clover(w->t1.p, ie, 0, 1, nrhs);
-  clover(w->t2.p, io, 1, 1, nrhs);
-  hop(oe, w->t2.p, ie, 0, 1, false, 1.0, nrhs);
-  hop(oo, w->t1.p, io, 1, 1, false, 1.0, nrhs);
+  clover_both(w->t1.p, w->t2.p, ie, io, 1, nrhs);
+  hop_both(oe, oo, w->t1.p, w->t2.p, ie, io, 1, nrhs);
+}
+
+// Operators on canonical spinors.  The launches that touch the caller's
+// vectors only site by site (the clover launch, the last hop) read and write
+// them directly; only a spinor whose neighbours are gathered is converted.
+// 24^3x64, us: D_r FP64 569 -> 485, D_r A_ee FP32 with 12 right-hand sides
+// 2900 -> 1790 (with the kernels for batches).
+void FineOp::apply(int op, bool dag, void* canon_out, const void* canon_in, int nrhs) {
+  const Geom& g = F->g;
+  w->ensure(prec, g, nrhs);
+  const size_t V12 = (size_t)g.V * 12;
+  const double2* in = reinterpret_cast<const double2*>(canon_in);
+  auto buf = [&](int slot) { return ctx->scratch_buf(slot, hb() * nrhs); };
+  auto last_hop = [&](double coeff) {
+    DslashArgs a = hop_args(coeff, nrhs);
+    a.canon_out = reinterpret_cast<double2*>(canon_out);
+    a.canon_stride = V12;
+    return a;
+  };
+  auto first_clover = [&] {
+    CloverArgs a = clover_args(1, nrhs);
+    a.canon_in = in;
+    a.canon_stride = V12;
+    return a;
+  };
+  if (op == WCMG_OP_FULL || (op == WCMG_OP_DP && dag)) {
+    // D, and D^dag = gamma5 D gamma5
+    void* ie = buf(42);
+    void* io = buf(43);
+    spinor_to_internal(prec, ie, io, canon_in, g, dag, st, nrhs);
+    if (op == WCMG_OP_DP) {
+      // D_p^dag = A^-1 gamma5 D gamma5
+      void* oe = buf(44);
+      void* oo = buf(45);
+      D(oe, oo, ie, io, nrhs);
+      CloverArgs a = clover_args(1, nrhs);
+      a.both = 1;
+      a.in = oe;
+      a.in2 = oo;
+      a.g5 = 1;
+      a.canon_out = reinterpret_cast<double2*>(canon_out);
+      a.canon_stride = V12;
+      run_clover(a);
+      return;
+    }
+    DslashArgs a = last_hop(1.0);
+    a.both = 1;
+    a.in = io;
+    a.x = ie;
+    a.in2 = ie;
+    a.x2 = io;
+    a.g5_out = dag;
+    run_hop(a, 2, false);
+  } else if (op == WCMG_OP_DP) {
+    CloverArgs ca = first_clover();
+    ca.both = 1;
+    ca.out = w->t1.p;
+    ca.out2 = w->t2.p;
+    run_clover(ca);
+    DslashArgs a = last_hop(1.0);
+    a.both = 1;
+    a.in = w->t2.p;
+    a.in2 = w->t1.p;
+    a.canon_x = in;
+    run_hop(a, 1, false);
+  } else if (op == WCMG_OP_SCHUR_X) {
+    // A_ee x - H_eo A_oo^-1 H_oe x; its adjoint is the same between gamma5s
+    void* ie = buf(42);
+    spinor_to_internal(prec, ie, nullptr, canon_in, g, dag, st, nrhs);
+    hop(w->t2.p, ie, nullptr, 1, 0, true, 1.0, nrhs);
+    DslashArgs a = last_hop(-1.0);
+    a.in = w->t2.p;
+    a.x = ie;
+    a.g5_out = dag;
+    a.zero_other = 1;
+    run_hop(a, 2, false);
+  } else {
+    // D_r, or D_r^dag = gamma5 (1 - A_ee^-1 H_eo A_oo^-1 H_oe) gamma5
+    if (dag) {
+      spinor_to_internal(prec, w->t1.p, nullptr, canon_in, g, true, st, nrhs);
+    } else {
+      CloverArgs ca = first_clover();
+      ca.out = w->t1.p;
+      run_clover(ca);
+    }
+    hop(w->t2.p, w->t1.p, nullptr, 1, 0, true, 1.0, nrhs);
+    DslashArgs a = last_hop(-1.0);
+    a.in = w->t2.p;
+    a.canon_x = in;
+    a.g5_x = dag;
+    a.g5_out = dag;
+    a.zero_other = 1;
+    run_hop(a, 1, dag);
+  }
 }
 
 void FineOp::reduced_source(void* br, const void* be, const void* bo, int nrhs) {

@@ -42,23 +42,27 @@ struct Tuner {
     int threads, group;
     double us;
   };
-  std::map<std::array<int, 5>, Choice> best;
+  std::map<std::array<int, 6>, Choice> best;
 };
 
 // ------------------------------------------------------------------ reductions
 struct Reducer {
   hipStream_t st = nullptr;
-  DBuf partial, res, counter;
-  DBuf part_b;  // per-block partials of the batched reductions
+  // one allocation: per-block partials (single vectors, batches), results, arrival counters
+  DBuf mem;
+  double* partial = nullptr;
+  double* part_b = nullptr;
+  double* res = nullptr;
+  unsigned* counter = nullptr;
   double* host = nullptr;  // pinned staging buffer for results read on the host
   void init(hipStream_t s);
-  double* dres() { return res.as<double>(); }
+  double* dres() { return res; }
   // reduction result to the device buffer `dst` (default: res)
   RedOut out(double* dst = nullptr) {
-    return RedOut{dst ? dst : res.as<double>(), partial.as<double>(), counter.as<unsigned>(), nullptr};
+    return RedOut{dst ? dst : res, partial, counter, nullptr};
   }
   // copy n results (from res, or from any device address) to the host and synchronise
-  const double* fetch(int n) { return fetch_from(res.as<double>(), n); }
+  const double* fetch(int n) { return fetch_from(res, n); }
   const double* fetch_from(const double* dev, int n);
   // rows doubles at dev + r * pitch (r < rows), `width` each, packed to host[r * width]
   const double* fetch_rows(const double* dev, size_t pitch, int width, int rows);
@@ -68,7 +72,7 @@ struct Reducer {
   hipEvent_t ev2[2] = {nullptr, nullptr};
   void fetch_async(const double* dev, int n, int slot);
   const double* fetch_wait(int slot);
-  RedB outb(double* dst, size_t rs) { return RedB{dst, rs, part_b.as<double>(), counter.as<unsigned>()}; }
+  RedB outb(double* dst, size_t rs) { return RedB{dst, rs, part_b, counter}; }
   ~Reducer();
 };
 
@@ -107,6 +111,15 @@ struct FineOp {
   void hop(void* out, const void* in, const void* x, int parity, int diag, bool postinv, double coeff,
            int nrhs = 1);
   void clover(void* out, const void* in, int parity, int kind, int nrhs = 1);
+  // the same on both parities in one launch (the hop with coefficient 1)
+  void hop_both(void* oe, void* oo, const void* ie, const void* io, const void* xe, const void* xo, int diag, int nrhs);
+  void clover_both(void* oe, void* oo, const void* ie, const void* io, int kind, int nrhs);
+  DslashArgs hop_args(double coeff, int nrhs) const;
+  CloverArgs clover_args(int kind, int nrhs) const;
+  void run_hop(DslashArgs& a, int diag, bool postinv);  // with the tuner's shape and the timers
+  void run_clover(const CloverArgs& a);
+  // operator `op` or its adjoint on nrhs canonical spinors (device)
+  void apply(int op, bool dag, void* canon_out, const void* canon_in, int nrhs);
   // reduced operator D_r y = y - H_eo A_oo^-1 H_oe A_ee^-1 y on even halves
   void Dr(void* out, const void* y, int nrhs = 1);
   // Dr with <out, y> and ||out||^2 reduced into o by its last launch; false

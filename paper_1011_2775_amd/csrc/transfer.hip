@@ -559,19 +559,14 @@ __global__ void k_vec_half_rounded(const double2* __restrict__ v64, float2* __re
     const size_t kpb = t / half;
     const size_t at = kpb * 2 * half * 6 + (size_t)l * 6;
     cpx<float> v[12];
-    float m = 0.f;
 #pragma unroll
     for (int a = 0; a < 12; ++a) {
       const double2 d = v64[at + (a >= 6 ? (size_t)half * 6 - 6 : 0) + a];
       v[a] = mk((float)d.x, (float)d.y);
-      m = fmaxf(m, fmaxf(fabsf(v[a].r), fabsf(v[a].i)));
     }
-    const float sc = m > 0.f ? m : 1.f, inv = 1.f / sc;
+    round_half_spinor(v);
 #pragma unroll
-    for (int a = 0; a < 12; ++a) {
-      const float2 f = __half22float2(__floats2half2_rn(v[a].r * inv, v[a].i * inv));
-      out[at + (a >= 6 ? (size_t)half * 6 - 6 : 0) + a] = make_float2(f.x * sc, f.y * sc);
-    }
+    for (int a = 0; a < 12; ++a) out[at + (a >= 6 ? (size_t)half * 6 - 6 : 0) + a] = make_float2(v[a].r, v[a].i);
   }
 }
 

@@ -273,6 +273,26 @@ struct SpinorIO<__half> {
   }
 };
 
+// The values an F16 spinor holds of v (stored and loaded back).  The packed
+// word passes through an empty asm: without it the multiplication and the
+// rounding to half are fused into one instruction, which rounds once where the
+// stored spinor is rounded twice.
+__device__ __forceinline__ void round_half_spinor(cpx<float> v[12]) {
+  float m = 0.f;
+#pragma unroll
+  for (int c = 0; c < 12; ++c) m = fmaxf(m, fmaxf(fabsf(v[c].r), fabsf(v[c].i)));
+  const float s = m > 0.f ? m : 1.f;
+  const float inv = 1.f / s;
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    const __half2 h = __floats2half2_rn(v[c].r * inv, v[c].i * inv);
+    unsigned w = *reinterpret_cast<const unsigned*>(&h);
+    asm volatile("" : "+v"(w));
+    const float2 f = __half22float2(*reinterpret_cast<const __half2*>(&w));
+    v[c] = mk(f.x * s, f.y * s);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // link and clover loads
 // ---------------------------------------------------------------------------
