@@ -1163,7 +1163,7 @@ int wcmg_force(void* ctx, int lat, void* dU, const void* psi, const void* lam, i
     const Geom& g = L.F.g;
     const bool clov = include_clover && (L.F.csw != 0.0 || L.F.csw_t != 0.0);
     const CloverCoef cc = clover_coef(L.F.csw, L.F.csw_t);
-    void* z = clov ? c->scratch_buf(52, (size_t)g.V * 54 * 16) : nullptr;
+    void* z = clov ? c->scratch_buf(52, (size_t)g.V * 54 * 8) : nullptr;
     force_compute(dU, psi, lam, nrhs, L.F.gauge[WCMG_F64].p, g, clov ? &cc : nullptr, z, c->st);
   });
 }

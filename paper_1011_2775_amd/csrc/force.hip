@@ -49,8 +49,7 @@ __device__ __forceinline__ void one_pm_gamma(const cpx<double> v[12], cpx<double
 
 template <int MU>
 __device__ __forceinline__ void hop_force_mu(const double2* x, const double2* lam, int nrhs, size_t V,
-                                             size_t y, size_t yp, double ph, double2* G) {
-  cpx<double> acc[9];
+                                             size_t y, size_t yp, double ph, cpx<double> acc[9]) {
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = mk(0.0, 0.0);
   for (int r = 0; r < nrhs; ++r) {
@@ -77,42 +76,42 @@ __device__ __forceinline__ void hop_force_mu(const double2* x, const double2* la
 #pragma unroll
         for (int b = 0; b < 3; ++b) cfmac(acc[a * 3 + b], l[s * 3 + b], w[s * 3 + a]);
   }
-  double2* o = G + (y * 4 + MU) * 9;
 #pragma unroll
-  for (int k = 0; k < 9; ++k) o[k] = make_double2(0.5 * ph * acc[k].r, 0.5 * ph * acc[k].i);
+  for (int k = 0; k < 9; ++k) acc[k] = (0.5 * ph) * acc[k];
 }
 
-__global__ void __launch_bounds__(kT) k_hop_force(double2* G, const double2* x, const double2* lam, int nrhs,
-                                                  DGeom g, int V) {
-  const int y = blockIdx.x * blockDim.x + threadIdx.x;
-  if (y >= V) return;
-  int c[4], n[4];
-  coords_of(g.L, y, c);
-  const double pht = (c[3] == g.L[3] - 1) ? g.t_bc : 1.0;
-  // spatial hops carry the coefficient g.hs (1 on isotropic lattices)
-  shift(g.L, c, 0, 1, n);
-  hop_force_mu<0>(x, lam, nrhs, V, y, lex_of(g.L, n), g.hs, G);
-  shift(g.L, c, 1, 1, n);
-  hop_force_mu<1>(x, lam, nrhs, V, y, lex_of(g.L, n), g.hs, G);
-  shift(g.L, c, 2, 1, n);
-  hop_force_mu<2>(x, lam, nrhs, V, y, lex_of(g.L, n), g.hs, G);
-  shift(g.L, c, 3, 1, n);
-  hop_force_mu<3>(x, lam, nrhs, V, y, lex_of(g.L, n), pht, G);
+// site of place t (parity p = t / Vh, checkerboard index t mod Vh): coordinates and lexicographic index
+__device__ __forceinline__ int force_site(const DGeom& g, int t, int c[4]) {
+  const int p = t >= g.Vh, i = t - p * g.Vh;
+  cb_coords(g, i, p, c);
+  return 2 * i + (c[0] & 1);
 }
 
-// Z[plane][9][V] = (Xi^dag - Xi) / 8 per site and plane mu < nu
-__global__ void __launch_bounds__(kT) k_clover_insertion(double2* Z, const double2* x, const double2* lam,
-                                                         int nrhs, CloverCoef cc, int V) {
-  const int y = blockIdx.x * blockDim.x + threadIdx.x;
-  if (y >= V) return;
+// Z = (Xi^dag - Xi) / 8 per site and plane mu < nu.  It is antihermitian: nine
+// doubles, [plane] of (01), (02), (12), (im 00, im 11) as double2[parity][Vh],
+// then im 22 as double[parity][Vh]
+// (ONE: one pair, whose spinors are loaded once for the six planes)
+template <bool ONE>
+__global__ void __launch_bounds__(kT) k_clover_insertion(double* Z, const double2* x, const double2* lam,
+                                                         int nrhs, CloverCoef cc, DGeom g) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x, V = 2 * g.Vh;
+  if (t >= V) return;
+  int c[4];
+  const int y = force_site(g, t, c);
+  cpx<double> v[12], l[12];
+  if constexpr (ONE) {
+    load12(x, y, v);
+    load12(lam, y, l);
+  }
   for (int pl = 0; pl < 6; ++pl) {
     cpx<double> xi[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) xi[k] = mk(0.0, 0.0);
-    for (int r = 0; r < nrhs; ++r) {
-      cpx<double> v[12], l[12];
-      load12(x, (size_t)r * V + y, v);
-      load12(lam, (size_t)r * V + y, l);
+    for (int r = 0; r < (ONE ? 1 : nrhs); ++r) {
+      if constexpr (!ONE) {
+        load12(x, (size_t)r * V + y, v);
+        load12(lam, (size_t)r * V + y, l);
+      }
 #pragma unroll
       for (int chi = 0; chi < 2; ++chi)
 #pragma unroll
@@ -126,35 +125,27 @@ __global__ void __launch_bounds__(kT) k_clover_insertion(double2* Z, const doubl
 #pragma unroll
               for (int j = 0; j < 3; ++j) {
                 // s * x_{sb,i} * conj(lambda_{sa,j})
-                cpx<double> t = mk(0.0, 0.0);
-                cfmac(t, l[sa * 3 + j], v[sb * 3 + i]);
-                cfma(xi[i * 3 + j], s, t);
+                cpx<double> u = mk(0.0, 0.0);
+                cfmac(u, l[sa * 3 + j], v[sb * 3 + i]);
+                cfma(xi[i * 3 + j], s, u);
               }
           }
     }
+    double* zp = Z + (size_t)pl * 9 * V;
+    double2* zo = reinterpret_cast<double2*>(zp);
+    constexpr int kRow[3] = {0, 0, 1}, kCol[3] = {1, 2, 2};
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        cpx<double> z = 0.125 * (cconj(xi[j * 3 + i]) - xi[i * 3 + j]);
-        Z[((size_t)pl * 9 + i * 3 + j) * V + y] = make_double2(z.r, z.i);
-      }
+    for (int k = 0; k < 3; ++k) {
+      const cpx<double> z = 0.125 * (cconj(xi[kCol[k] * 3 + kRow[k]]) - xi[kRow[k] * 3 + kCol[k]]);
+      zo[(size_t)k * V + t] = make_double2(z.r, z.i);
+    }
+    zo[(size_t)3 * V + t] = make_double2(-0.25 * xi[0].i, -0.25 * xi[4].i);
+    zp[(size_t)8 * V + t] = -0.25 * xi[8].i;
   }
 }
 
 __device__ __forceinline__ int plane_index(int a, int b) {  // a < b
   return a == 0 ? b - 1 : (a == 1 ? b + 1 : 5);
-}
-
-__device__ __forceinline__ C3 load_z(const double2* Z, int pl, int V, const int L[4], const int c[4]) {
-  const int y = lex_of(L, c);
-  C3 m;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) {
-    double2 t = Z[((size_t)pl * 9 + k) * V + y];
-    m.m[k] = mk(t.x, t.y);
-  }
-  return m;
 }
 
 __device__ __forceinline__ C3 madd(const C3& a, const C3& b) {
@@ -164,85 +155,174 @@ __device__ __forceinline__ C3 madd(const C3& a, const C3& b) {
   return r;
 }
 
-// derivative matrix K_k of square z in plane (a, b) with respect to its factor k (1..4)
-__device__ C3 square_derivative(const double2* gauge, const double2* Z, const DGeom& g, int V, int a, int b,
-                                const int z[4], int k) {
-  const int pl = plane_index(a, b);
-  int c[4][4];  // corners c1..c4 -> c[0..3]
-#pragma unroll
-  for (int d = 0; d < 4; ++d) c[0][d] = z[d];
-  shift(g.L, z, a, 1, c[1]);
-  shift(g.L, c[1], b, 1, c[2]);
-  shift(g.L, z, b, 1, c[3]);
-  // factor j (0-based) starts at corner j: L1 = U_a(c1), L2 = U_b(c2), L3 = U_a(c4)^dag, L4 = U_b(c1)^dag
-  auto factor = [&](int j) -> C3 {
-    switch (j) {
-      case 0: return load_u(gauge, g, c[0], a);
-      case 1: return load_u(gauge, g, c[1], b);
-      case 2: return dagm(load_u(gauge, g, c[3], a));
-      default: return dagm(load_u(gauge, g, c[0], b));
-    }
-  };
-  const int k0 = k - 1;
-  const int j1 = (k0 + 1) & 3, j2 = (k0 + 2) & 3, j3 = (k0 + 3) & 3;
-  const C3 A = factor(j1), B = factor(j2), C = factor(j3);
-  const C3 Z1 = load_z(Z, pl, V, g.L, c[j1]);
-  const C3 Z2 = load_z(Z, pl, V, g.L, c[j2]);
-  const C3 Z3 = load_z(Z, pl, V, g.L, c[j3]);
-  const C3 Z0 = load_z(Z, pl, V, g.L, c[k0]);
-  const C3 AB = mul(A, B);
-  const C3 T1 = madd(mul(Z1, A), mul(A, Z2));
-  const C3 T2 = madd(mul(T1, B), mul(AB, Z3));
-  const C3 ABC = mul(AB, C);
-  return madd(mul(T2, C), mul(ABC, Z0));
+// One wavefront per direction mu of 64 sites, the four of a workgroup on the
+// same sites: they share links and Z through the L1, mu and nu are scalar (a
+// thread per link with mu in the low bits of its index had the lanes of a
+// wavefront in different directions: every load four groups of sites, both
+// branches of every square), the sites of a wavefront are neighbours in the
+// checkerboard layout, and a link's two parts are written once.
+//
+// For link U_mu(x) and direction nu, with Z of the plane (antihermitian) and
+// the path x -> x +- nu -> x +- nu + mu -> x + mu of links A, B, C (A and C
+// adjoint where the path runs against them),
+//   K = Z(x) A B C + A Z(x +- nu) B C + A B Z(x +- nu + mu) C + A B C Z(x + mu)
+// is the derivative of the square on that side with the link taken out: the
+// square above nu contributes -K and the one below +K for mu < nu (the reverse
+// orientation, mu > nu, the negative), written as
+//   A (Z B + B Z) C + Z(x) A B C + A B C Z(x + mu)
+// with products formed in place: the sum over both sides kept apart (four more
+// matrices alive) took 372 registers, one wavefront per SIMD and 316 us; loads
+// held behind what stands before them (fewer registers still) 390 us; 256
+// registers, two wavefronts, loads free within a square, 262 us.
+// 48 products of 3x3 matrices a link (90 us of FP64 arithmetic at this size)
+// and the gather of 18 links and 24 Z of 72 bytes through L1 and L2 bound it.
+// 16^3x32, one pair of spinors: hop part 87 us and clover part 614 us as
+// launches of their own, 262 us now; the insertion 63 us, 29 us now.
+struct ForceLinks {
+  const double2* gauge;
+  const double* Z;
+  DGeom g;
+};
+__device__ __forceinline__ C3 load_zc(const ForceLinks& f, int pl, const int c[4]) {
+  const int p = (c[0] + c[1] + c[2] + c[3]) & 1;
+  const size_t V = 2 * (size_t)f.g.Vh, t = (size_t)p * f.g.Vh + cb_index(f.g, c);
+  const double* zp = f.Z + (size_t)pl * 9 * V;
+  const double2* b = reinterpret_cast<const double2*>(zp) + t;
+  const double2 z01 = b[0], z02 = b[V], z12 = b[2 * V], d = b[3 * V];
+  const double d2 = zp[8 * V + t];
+  C3 m;
+  m.m[0] = mk(0.0, d.x);
+  m.m[1] = mk(z01.x, z01.y);
+  m.m[2] = mk(z02.x, z02.y);
+  m.m[3] = mk(-z01.x, z01.y);
+  m.m[4] = mk(0.0, d.y);
+  m.m[5] = mk(z12.x, z12.y);
+  m.m[6] = mk(-z02.x, z02.y);
+  m.m[7] = mk(-z12.x, z12.y);
+  m.m[8] = mk(0.0, d2);
+  return m;
 }
 
-// G[(y*4+mu)*9 ..] += clover part, one thread per link
-__global__ void __launch_bounds__(kT) k_clover_force(double2* G, const double2* Z, const double2* gauge, DGeom g,
-                                                     int V) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 4 * V) return;
-  const int y = t >> 2, mu = t & 3;
-  int x[4];
-  coords_of(g.L, y, x);
-  C3 acc;
+// acc += s A B
+__device__ __forceinline__ void mul_add(C3& acc, double s, const C3& A, const C3& B) {
 #pragma unroll
-  for (int k = 0; k < 9; ++k) acc.m[k] = mk(0.0, 0.0);
-  for (int nu = 0; nu < 4; ++nu) {
-    if (nu == mu) continue;
-    int z[4];
-    if (mu < nu) {
-      // U_mu(x) is factor 1 of square z = x and factor 3 (adjoint) of square z = x - nu
-      acc = madd(acc, dagm(square_derivative(gauge, Z, g, V, mu, nu, x, 1)));
-      shift(g.L, x, nu, -1, z);
-      acc = madd(acc, square_derivative(gauge, Z, g, V, mu, nu, z, 3));
-    } else {
-      // U_mu(x) is factor 2 of square z = x - nu and factor 4 (adjoint) of square z = x
-      shift(g.L, x, nu, -1, z);
-      acc = madd(acc, dagm(square_derivative(gauge, Z, g, V, nu, mu, z, 2)));
-      acc = madd(acc, square_derivative(gauge, Z, g, V, nu, mu, x, 4));
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const cpx<double> a = s * A.m[i * 3 + k];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) cfma(acc.m[i * 3 + j], a, B.m[k * 3 + j]);
+    }
+}
+// B <- A B, column by column; B <- B A, row by row
+__device__ __forceinline__ void left_mul(const C3& A, C3& B) {
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    cpx<double> t[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      t[i] = mk(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) cfma(t[i], A.m[i * 3 + k], B.m[k * 3 + j]);
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) B.m[i * 3 + j] = t[i];
+  }
+}
+__device__ __forceinline__ void right_mul(C3& B, const C3& A) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    cpx<double> t[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      t[j] = mk(0.0, 0.0);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) cfma(t[j], B.m[i * 3 + k], A.m[k * 3 + j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) B.m[i * 3 + j] = t[j];
+  }
+}
+
+template <bool up>
+__device__ __forceinline__ void clover_force_side(const ForceLinks& f, const int x[4], const int xm[4], int mu, int nu,
+                                                  C3& acc) {
+  const int pl = mu < nu ? plane_index(mu, nu) : plane_index(nu, mu);
+  const double sgn = (mu < nu) != up ? 1.0 : -1.0;
+  int z[4], zm[4];
+  shift(f.g.L, x, nu, up ? 1 : -1, z);
+  shift(f.g.L, xm, nu, up ? 1 : -1, zm);
+  C3 B = load_u(f.gauge, f.g, z, mu), M;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) M.m[k] = mk(0.0, 0.0);
+  mul_add(M, 1.0, load_zc(f, pl, z), B);
+  mul_add(M, 1.0, B, load_zc(f, pl, zm));
+  {
+    const C3 A = up ? load_u(f.gauge, f.g, x, nu) : dagm(load_u(f.gauge, f.g, z, nu));
+    left_mul(A, M);
+    left_mul(A, B);
+  }
+  {
+    const C3 C = up ? dagm(load_u(f.gauge, f.g, xm, nu)) : load_u(f.gauge, f.g, zm, nu);
+    mul_add(acc, sgn, M, C);
+    right_mul(B, C);
+  }
+  mul_add(acc, sgn, load_zc(f, pl, x), B);
+  mul_add(acc, sgn, B, load_zc(f, pl, xm));
+}
+
+template <bool CLOVER>
+__global__ void __launch_bounds__(256, 2) k_link_force(double2* G, const double2* x, const double2* lam, int nrhs,
+                                                    ForceLinks f) {
+  const int V = 2 * f.g.Vh, nblocks = (V + 63) / 64, b = xcd_block(nblocks);
+  const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = b * 64 + (threadIdx.x & 63);
+  if (b >= nblocks || t >= V) return;
+  int c[4], cm[4];
+  const int y = force_site(f.g, t, c);
+  shift(f.g.L, c, mu, 1, cm);
+  const size_t yp = lex_of(f.g.L, cm);
+  // spatial hops carry the coefficient hs (1 on isotropic lattices), the last time slice its phase
+  const double ph = mu < 3 ? f.g.hs : (c[3] == f.g.L[3] - 1 ? f.g.t_bc : 1.0);
+  C3 acc;
+  if (mu == 0) hop_force_mu<0>(x, lam, nrhs, V, y, yp, ph, acc.m);
+  else if (mu == 1) hop_force_mu<1>(x, lam, nrhs, V, y, yp, ph, acc.m);
+  else if (mu == 2) hop_force_mu<2>(x, lam, nrhs, V, y, yp, ph, acc.m);
+  else hop_force_mu<3>(x, lam, nrhs, V, y, yp, ph, acc.m);
+  if constexpr (CLOVER) {
+#pragma unroll 1
+    for (int k = 1; k < 4; ++k) {
+      const int nu = (mu + k) & 3;
+      clover_force_side<true>(f, c, cm, mu, nu, acc);
+      clover_force_side<false>(f, c, cm, mu, nu, acc);
     }
   }
-  double2* o = G + (size_t)t * 9;
+  double2* o = G + ((size_t)y * 4 + mu) * 9;
 #pragma unroll
-  for (int k = 0; k < 9; ++k) o[k] = make_double2(o[k].x + acc.m[k].r, o[k].y + acc.m[k].i);
+  for (int k = 0; k < 9; ++k) o[k] = make_double2(acc.m[k].r, acc.m[k].i);
 }
 }  // namespace
 
 void force_compute(void* G, const void* x, const void* lam, int nrhs, const void* gauge64, const Geom& g,
                    const CloverCoef* cc, void* zbuf, hipStream_t st) {
-  const DGeom d = dgeom(g);
-  const int V = g.V;
-  hipLaunchKernelGGL(k_hop_force, dim3((V + kT - 1) / kT), dim3(kT), 0, st, reinterpret_cast<double2*>(G),
-                     reinterpret_cast<const double2*>(x), reinterpret_cast<const double2*>(lam), nrhs, d, V);
-  HIPCHK(hipGetLastError());
-  if (!cc) return;
-  hipLaunchKernelGGL(k_clover_insertion, dim3((V + kT - 1) / kT), dim3(kT), 0, st,
-                     reinterpret_cast<double2*>(zbuf), reinterpret_cast<const double2*>(x),
-                     reinterpret_cast<const double2*>(lam), nrhs, *cc, V);
-  HIPCHK(hipGetLastError());
-  hipLaunchKernelGGL(k_clover_force, dim3((4 * V + kT - 1) / kT), dim3(kT), 0, st, reinterpret_cast<double2*>(G),
-                     reinterpret_cast<const double2*>(zbuf), reinterpret_cast<const double2*>(gauge64), d, V);
+  ForceLinks f{reinterpret_cast<const double2*>(gauge64), reinterpret_cast<const double*>(zbuf), dgeom(g)};
+  const double2* xs = reinterpret_cast<const double2*>(x);
+  const double2* ls = reinterpret_cast<const double2*>(lam);
+  if (cc) {
+    const dim3 gz((g.V + kT - 1) / kT);
+    if (nrhs == 1)
+      hipLaunchKernelGGL(k_clover_insertion<true>, gz, dim3(kT), 0, st, reinterpret_cast<double*>(zbuf), xs, ls, nrhs,
+                         *cc, f.g);
+    else
+      hipLaunchKernelGGL(k_clover_insertion<false>, gz, dim3(kT), 0, st, reinterpret_cast<double*>(zbuf), xs, ls,
+                         nrhs, *cc, f.g);
+    HIPCHK(hipGetLastError());
+  }
+  const dim3 grid(xcd_grid((g.V + 63) / 64));
+  if (cc)
+    hipLaunchKernelGGL(k_link_force<true>, grid, dim3(256), 0, st, reinterpret_cast<double2*>(G), xs, ls, nrhs, f);
+  else
+    hipLaunchKernelGGL(k_link_force<false>, grid, dim3(256), 0, st, reinterpret_cast<double2*>(G), xs, ls, nrhs, f);
   HIPCHK(hipGetLastError());
 }
 
