@@ -382,7 +382,7 @@ void launch_coarse_right_mul(double* Yt, const double* Y, const double* Xinv, co
                              hipStream_t st);
 // canonical complex128 [lex][n] <-> internal [perm[lex]][n] (F64 or F32)
 void launch_coarse_canon(int prec, void* internal, void* canon, const int* perm, int V, int n, bool to_internal,
-                         hipStream_t st);
+                         hipStream_t st, int nrhs = 1);
 void launch_reals_convert(int prec_dst, void* dst, const double* src, size_t n, hipStream_t st);
 
 }  // namespace wcmg

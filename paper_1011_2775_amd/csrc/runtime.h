@@ -342,7 +342,8 @@ size_t coarse_solve_noalloc_bytes(const CoarseLevel& C, int prec, int restart, i
 // the persistent coarse solve (wcmg_coarse_solve, launch 0) with every buffer carved
 // from `base` (at least coarse_solve_noalloc_bytes); x, b canonical complex128 [Vc][n]
 void coarse_solve_noalloc(Ctx& c, CoarseLevel& C, int prec, void* base, int grid, void* x, const void* b,
-                          double tol, int max_iter, int restart, wcmg_stats* s);
+                          double tol, int max_iter, int restart, bool general, bool mat16, wcmg_stats* s);
+void coarse_residual(Ctx& c, CoarseLevel& C, int prec, const void* x, const void* b, void* t, wcmg_stats* s);
 KrylovResult bicgstab(Ctx& c, int prec, size_t n, const OpFn& A, void* x, const void* b, double tol,
                       double target_norm, int maxiter);
 // batched flexible GCR: A and K act on S.nrhs right-hand sides at once

@@ -724,6 +724,8 @@ NoAllocPlan plan_noalloc(Carve& k, const CoarseLevel& C, int prec, int restart, 
   const size_t nall = (size_t)C.cg.V * C.cg.n, hv = (size_t)C.cg.Vh * C.cg.n;
   NoAllocPlan P{};
   P.B.ctl = k.take(kPersistCtlBytes);  // first: the control block is cleared at every call
+  P.B.tag_bytes = coarse_gcr_persistent_tag_bytes(C.cg.n, C.cg.Vh, grid);
+  P.B.tags = k.take(P.B.tag_bytes);    // ... and the tags behind it with it
   P.B.part = reinterpret_cast<double*>(k.take(2 * (size_t)grid * coarse_gcr_persistent_part_doubles() * 8));
   P.vb = k.take(nall * cs);
   P.vx = k.take(nall * cs);
@@ -735,8 +737,6 @@ NoAllocPlan plan_noalloc(Carve& k, const CoarseLevel& C, int prec, int restart, 
   P.B.Z = k.take((size_t)restart * hv * cs);
   P.B.T = k.take((size_t)restart * 2 * hv * cs);
   P.B.qraw = k.take(hv * cs);
-  P.B.tag_bytes = coarse_gcr_persistent_tag_bytes(C.cg.n, C.cg.Vh, grid);
-  P.B.tags = k.take(P.B.tag_bytes);
   return P;
 }
 }  // namespace
@@ -747,19 +747,28 @@ size_t coarse_solve_noalloc_bytes(const CoarseLevel& C, int prec, int restart, i
   return k.used;
 }
 
+// ||b - Yhat x|| / ||b|| of the full coarse system (t: work vector)
+void coarse_residual(Ctx& c, CoarseLevel& C, int prec, const void* x, const void* b, void* t, wcmg_stats* s) {
+  const size_t nall = (size_t)C.cg.V * C.cg.n;
+  CoarseOp op{&C, prec, nullptr, c.st};
+  op.Dfull(t, x);
+  blas_axpy_norm(prec, -1.0, 0.0, b, t, nall, c.red.out(), c.st);
+  blas_norm2(prec, b, nall, c.red.out(c.red.dres() + 1), c.st);
+  const double* n2 = c.red.fetch(2);
+  s->true_rel_res = n2[1] > 0 ? std::sqrt(n2[0] / n2[1]) : 0.0;
+}
+
 void coarse_solve_noalloc(Ctx& c, CoarseLevel& C, int prec, void* base, int grid, void* x, const void* b,
-                          double tol, int max_iter, int restart, wcmg_stats* s) {
+                          double tol, int max_iter, int restart, bool general, bool mat16, wcmg_stats* s) {
   Carve k{reinterpret_cast<char*>(base)};
   restart = std::min(restart, std::max(1, max_iter));
   NoAllocPlan P = plan_noalloc(k, C, prec, restart, grid);
-  const size_t nall = (size_t)C.cg.V * C.cg.n;
   // the previous call's barrier epochs, counters, status words and tags are not ours
-  noalloc_zero(P.B.ctl, kPersistCtlBytes, c.st);
-  noalloc_zero(P.B.tags, P.B.tag_bytes, c.st);
+  noalloc_zero(P.B.ctl, reinterpret_cast<char*>(P.B.tags) + P.B.tag_bytes - reinterpret_cast<char*>(P.B.ctl), c.st);
   launch_coarse_canon(prec, P.vb, const_cast<void*>(b), C.perm.as<int>(), C.cg.V, C.cg.n, true, c.st);
   auto t0 = std::chrono::steady_clock::now();
   persistent_launch_bufs(c, grid, P.B, C, prec, P.vx, P.vb, P.t, P.y, P.r, P.br, tol, restart, max_iter, false,
-                         false);
+                         general, mat16);
   // iterations, status and the barrier-abort flag of the launch (pinned staging, no allocation)
   HIPCHK(hipMemcpyAsync(c.red.host, reinterpret_cast<char*>(P.B.ctl) + kPersistInfoOffset, 3 * sizeof(int),
                         hipMemcpyDeviceToHost, c.st));
@@ -771,12 +780,7 @@ void coarse_solve_noalloc(Ctx& c, CoarseLevel& C, int prec, void* base, int grid
   st.status = info[1];
   st.t_solve_s = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   launch_coarse_canon(prec, P.vx, x, C.perm.as<int>(), C.cg.V, C.cg.n, false, c.st);
-  // ||b - Yhat x|| / ||b|| of the full coarse system
-  CoarseOp op{&C, prec, nullptr, c.st};
-  op.Dfull(P.t, P.vx);
-  blas_axpby(prec, 1.0, 0.0, P.vb, -1.0, 0.0, P.t, nall, c.st);
-  const double rr = norm2(c, prec, P.t, nall), bb = norm2(c, prec, P.vb, nall);
-  st.true_rel_res = bb > 0 ? std::sqrt(rr / bb) : 0.0;
+  coarse_residual(c, C, prec, P.vx, P.vb, P.t, &st);
   if (s) *s = st;
 }
 
