@@ -52,6 +52,26 @@ __global__ void __launch_bounds__(kThreads) k_cdot_norm_b(const void* x, const v
   reduce_rhs(v, o);
 }
 
+template <typename T>
+__global__ void k_zero_b(void* x, size_t vs, size_t n) {
+  void* xr = row<T>(x, vs);
+  GRID_STRIDE(i, n) st<T>(xr, i, mk(0.0, 0.0));
+}
+template <typename T>
+__global__ void k_copy_b(void* y, const void* x, size_t vs, size_t n) {
+  void* yr = row<T>(y, vs);
+  const void* xr = row<T>(x, vs);
+  GRID_STRIDE(i, n) st<T>(yr, i, ld<T>(xr, i));
+}
+// out = b - y (out may be y)
+template <typename T>
+__global__ void k_residual_b(void* out, const void* b, const void* y, size_t vs, size_t n) {
+  void* o = row<T>(out, vs);
+  const void* br = row<T>(b, vs);
+  const void* yr = row<T>(y, vs);
+  GRID_STRIDE(i, n) st<T>(o, i, ld<T>(br, i) - ld<T>(yr, i));
+}
+
 // MR step of every right-hand side with alpha = coef[0..1] / coef[2] (row r at coef + r * cs)
 template <typename T>
 __global__ void k_mr_update_b(const double* coef, size_t cs, void* x, void* r, const void* Ar, size_t vs, size_t n) {
@@ -94,6 +114,20 @@ void blas_cdot_norm_b(int prec, const void* x, const void* y, size_t vs, size_t 
                       hipStream_t st) {
   check_batch(nrhs);
   DISPATCH_B(prec, k_cdot_norm_b, red_grid_b(n, nrhs), x, y, vs, n, o);
+}
+
+void blas_zero_b(int prec, void* x, size_t vs, size_t n, int nrhs, hipStream_t st) {
+  check_batch(nrhs);
+  if (n) DISPATCH_B(prec, k_zero_b, ew_grid_b(n, nrhs), x, vs, n);
+}
+void blas_copy_b(int prec, void* y, const void* x, size_t vs, size_t n, int nrhs, hipStream_t st) {
+  check_batch(nrhs);
+  if (n) DISPATCH_B(prec, k_copy_b, ew_grid_b(n, nrhs), y, x, vs, n);
+}
+void blas_residual_b(int prec, void* out, const void* b, const void* y, size_t vs, size_t n, int nrhs,
+                     hipStream_t st) {
+  check_batch(nrhs);
+  if (n) DISPATCH_B(prec, k_residual_b, ew_grid_b(n, nrhs), out, b, y, vs, n);
 }
 
 void blas_mr_update_b(int prec, const double* coef, size_t cs, void* x, void* r, const void* Ar, size_t vs, size_t n,

@@ -96,6 +96,10 @@ void spinor_to_internal(int prec, void* even, void* odd, const void* canon, cons
 void spinor_from_internal(int prec, void* canon, const void* even, const void* odd, const Geom& g, bool g5,
                           hipStream_t st, int nrhs = 1);
 // one parity, any precision pair
+// last MR step of a smoother, e + alpha r with alpha as blas_mr_update_dev, rounded to prec (F64 or
+// F32) and written as FP64; fields back to back, coefficients of right-hand side i at coef + i * cs
+void spinor_mr_last(int prec, void* dst64, const double* coef, size_t cs, const void* e, const void* r, int Vh,
+                    int nrhs, hipStream_t st);
 void spinor_convert(int prec_dst, void* dst, int prec_src, const void* src, int Vh, hipStream_t st);
 void spinor_gamma5(int prec, void* v, int Vh, hipStream_t st);
 
@@ -206,6 +210,11 @@ void blas_gcr_step_b(int prec, const void* const* q, int k, void* y, const void*
 void blas_gcr_update_x_raw_b(int prec, const void* const* z, int kt, void* x, size_t vs, size_t n, int nrhs,
                              const double* qa, size_t qs, const double* cmat, size_t cms, int ldc, double* y,
                              size_t ys, hipStream_t st);
+// element operations on every right-hand side of a batch, one launch: x = 0, y = x, out = b - y (out may be y)
+void blas_zero_b(int prec, void* x, size_t vs, size_t n, int nrhs, hipStream_t st);
+void blas_copy_b(int prec, void* y, const void* x, size_t vs, size_t n, int nrhs, hipStream_t st);
+void blas_residual_b(int prec, void* out, const void* b, const void* y, size_t vs, size_t n, int nrhs,
+                     hipStream_t st);
 void blas_mr_update_b(int prec, const double* coef, size_t cs, void* x, void* r, const void* Ar, size_t vs, size_t n,
                       int nrhs, hipStream_t st);
 

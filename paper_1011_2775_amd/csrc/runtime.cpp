@@ -133,12 +133,19 @@ void Reducer::init(hipStream_t s) {
   HIPCHK(hipHostMalloc((void**)&host2, 16 * sizeof(double), hipHostMallocDefault));
   for (auto& e : ev2) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
 }
-const double* Reducer::fetch_rows(const double* dev, size_t pitch, int width, int rows) {
+void Reducer::fetch_rows_async(const double* dev, size_t pitch, int width, int rows) {
   if (width * rows > 256) fail(WCMG_EINVAL, "too many scalars for the host staging buffer");
   HIPCHK(hipMemcpy2DAsync(host, (size_t)width * sizeof(double), dev, pitch * sizeof(double),
                           (size_t)width * sizeof(double), rows, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
+  HIPCHK(hipEventRecord(ev2[0], st));
+}
+const double* Reducer::fetch_rows_wait() {
+  HIPCHK(hipEventSynchronize(ev2[0]));
   return host;
+}
+const double* Reducer::fetch_rows(const double* dev, size_t pitch, int width, int rows) {
+  fetch_rows_async(dev, pitch, width, rows);
+  return fetch_rows_wait();
 }
 // The copy is ordered after the reduction on the stream; values written by a
 // kernel straight into host-mapped memory were not reliably visible to the

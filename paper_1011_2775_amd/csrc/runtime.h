@@ -66,6 +66,9 @@ struct Reducer {
   const double* fetch_from(const double* dev, int n);
   // rows doubles at dev + r * pitch (r < rows), `width` each, packed to host[r * width]
   const double* fetch_rows(const double* dev, size_t pitch, int width, int rows);
+  // the same in two halves: work issued in between runs while the host waits for the copy
+  void fetch_rows_async(const double* dev, size_t pitch, int width, int rows);
+  const double* fetch_rows_wait();
   // two-slot asynchronous form: the copy of n <= 8 doubles is ordered on the
   // stream and completes while later work runs; fetch_wait blocks for it
   double* host2 = nullptr;

@@ -229,22 +229,16 @@ std::vector<KrylovResult> gcr_b(Ctx& c, GcrSpaceB& S, const OpFn& A, const OpFn*
   S.ensure(restart);
   const int prec = S.prec;
   const size_t n = S.n, vs = S.vs;
-  const size_t es = prec == WCMG_F64 ? 16 : 8;
   hipStream_t st = c.st;
   Reducer& R = c.red;
   void* r = S.r.p;
   std::vector<KrylovResult> res(nr);
-  auto each = [&](auto&& f) {
-    for (int i = 0; i < nr; ++i) f(i, (size_t)i * vs * es);
-  };
   if (x_zero) {
-    each([&](int, size_t o) {
-      blas_zero(prec, (char*)x + o, n, st);
-      blas_copy(prec, (char*)r + o, (const char*)b + o, n, st);
-    });
+    blas_zero_b(prec, x, vs, n, nr, st);
+    blas_copy_b(prec, r, b, vs, n, nr, st);
   } else {
     A(r, x);
-    each([&](int, size_t o) { blas_axpby(prec, 1.0, 0.0, (const char*)b + o, -1.0, 0.0, (char*)r + o, n, st); });
+    blas_residual_b(prec, r, b, r, vs, n, nr, st);
   }
   std::vector<double> rn2(nr), target(nr);
   std::vector<char> done(nr, 0), conv(nr, 0);
@@ -277,7 +271,7 @@ std::vector<KrylovResult> gcr_b(Ctx& c, GcrSpaceB& S, const OpFn& A, const OpFn*
   if (!(all && !fixed)) {
     while (iters < maxiter) {
       int k = 0;
-      bool stop = false;
+      bool stop = false, ahead = false;
       for (; k < restart;) {
         void* z = S.Z[k].p;
         void* q = S.Q[k].p;
@@ -289,8 +283,9 @@ std::vector<KrylovResult> gcr_b(Ctx& c, GcrSpaceB& S, const OpFn& A, const OpFn*
         if (K)
           (*K)(z, r);
         else if (k == 0)
-          each([&](int, size_t o) { blas_copy(prec, (char*)z + o, (const char*)r + o, n, st); });
-        A(q, z);
+          blas_copy_b(prec, z, r, vs, n, nr, st);
+        if (!ahead) A(q, z);
+        ahead = false;
         for (int j = 0; j < k; ++j) Dp[j] = Qp[j];
         Dp[k] = q;
         Dp[k + 1] = rin;
@@ -307,7 +302,15 @@ std::vector<KrylovResult> gcr_b(Ctx& c, GcrSpaceB& S, const OpFn& A, const OpFn*
           }
           continue;
         }
-        const double* o = R.fetch_rows(qa + 4 * k - 4, cs, 4, nr);
+        // the norms come to the host while the device already applies A to the next
+        // direction (one application too many at the end, 33 us in FP32 on 512 sites
+        // x 48 and 12 vectors, against 20 us of idle device at every step)
+        R.fetch_rows_async(qa + 4 * k - 4, cs, 4, nr);
+        if (!K && k < restart && iters < maxiter) {
+          A(S.Q[k].p, S.Z[k].p);
+          ahead = true;
+        }
+        const double* o = R.fetch_rows_wait();
         all = true;
         for (int i = 0; i < nr; ++i) {
           const double qq = o[4 * i];
@@ -337,7 +340,7 @@ std::vector<KrylovResult> gcr_b(Ctx& c, GcrSpaceB& S, const OpFn& A, const OpFn*
       if (fixed) break;
       // true residuals at the end of every cycle
       A(r, x);
-      each([&](int, size_t o) { blas_axpby(prec, 1.0, 0.0, (const char*)b + o, -1.0, 0.0, (char*)r + o, n, st); });
+      blas_residual_b(prec, r, b, r, vs, n, nr, st);
       blas_norm2_b(prec, r, vs, n, nr, R.outb(R.dres(), 1), st);
       const double* h = R.fetch(nr);
       all = true;
@@ -1039,16 +1042,25 @@ struct MGSolver {
   // DrRed(out, in, o, e, coef): D_r with <out, in>, ||out||^2 reduced into o in
   // its own last launch, the pending update of e and in (coefficients coef,
   // previous D_r result in out) fused into its first (e null: none); returns
-  // false, launching nothing, where it does not apply
+  // false, launching nothing, where it does not apply.  z64: the smoothed e goes
+  // there, as an FP64 spinor field, instead of to e
   template <typename DrFn, typename DrRedFn>
   void mr_smooth(const DrFn& Dr, const DrRedFn& DrRed, int prec, void* e, const void* r, void* res, void* Ar,
-                 size_t n) {
-    const int nu = L.params.nu_post;
-    if (nu <= 0) return;
+                 size_t n, void* z64 = nullptr) {
+    const int nu = L.params.nu_post, Vh = L.F.g.Vh;
     hipStream_t st = c.st;
+    if (nu <= 0) {
+      if (z64) spinor_convert(WCMG_F64, z64, prec, e, Vh, st);
+      return;
+    }
     Dr(Ar, e);
-    blas_copy(prec, res, r, n, st);
-    blas_axpby(prec, -1.0, 0.0, Ar, 1.0, 0.0, res, n, st);
+    blas_residual_b(prec, res, r, Ar, n, n, 1, st);
+    auto update = [&](bool last) {
+      if (last && z64)
+        spinor_mr_last(prec, z64, c.red.dres(), 0, e, res, Vh, 1, st);
+      else
+        blas_mr_update_dev(prec, c.red.dres(), e, res, Ar, n, st);
+    };
     // alpha = <Ar, r> / ||Ar||^2 stays on the device: no host round trip; with the
     // fused D_r the update of step i runs inside the first launch of step i + 1
     bool pending = false;
@@ -1059,9 +1071,9 @@ struct MGSolver {
       }
       Dr(Ar, res);
       blas_cdot_norm(prec, Ar, res, n, c.red.out(), st);
-      blas_mr_update_dev(prec, c.red.dres(), e, res, Ar, n, st);
+      update(i + 1 == nu);
     }
-    if (pending) blas_mr_update_dev(prec, c.red.dres(), e, res, Ar, n, st);
+    if (pending) update(true);
   }
 
   // K_li(r_e) on coarse level li + 1: even part of P (next-level solve) R (r_e, 0), then MR
@@ -1176,8 +1188,7 @@ struct MGSolver {
               [&](void* o, void* i, const RedOut& ro, void* ee, const double* cf) {
                 return op.Dr_red(o, i, ro, ee, cf);
               },
-              sp, e_s.p, r_s.p, res_s.p, Ar_s.p, n);
-    spinor_convert(WCMG_F64, z64, sp, e_s.p, g.Vh, st);
+              sp, e_s.p, r_s.p, res_s.p, Ar_s.p, n, z64);
     ++calls;
   }
 
@@ -1200,23 +1211,28 @@ struct MGSolver {
     }
   }
 
-  // MR smoothing of nrhs right-hand sides (n elements each, vs apart) in lockstep
+  // MR smoothing of nrhs right-hand sides (n elements each, vs apart) in lockstep;
+  // z64 as in mr_smooth (fields back to back)
   template <typename DrFn>
   void mr_smooth_b(const DrFn& Dr, int prec, void* e, const void* r, void* res, void* Ar, size_t n, size_t vs,
-                   int nrhs) {
-    const int nu = L.params.nu_post;
-    if (nu <= 0) return;
+                   int nrhs, void* z64 = nullptr) {
+    const int nu = L.params.nu_post, Vh = L.F.g.Vh;
     hipStream_t st = c.st;
-    const size_t es = prec == WCMG_F64 ? 16 : 8;
-    Dr(Ar, e);
-    for (int i = 0; i < nrhs; ++i) {
-      const size_t o = (size_t)i * vs * es;
-      blas_copy(prec, (char*)res + o, (const char*)r + o, n, st);
-      blas_axpby(prec, -1.0, 0.0, (char*)Ar + o, 1.0, 0.0, (char*)res + o, n, st);
+    if (nu <= 0) {
+      const size_t es = prec == WCMG_F64 ? 16 : 8;
+      for (int i = 0; z64 && i < nrhs; ++i)
+        spinor_convert(WCMG_F64, (char*)z64 + i * vs * 16, prec, (char*)e + i * vs * es, Vh, st);
+      return;
     }
+    Dr(Ar, e);
+    blas_residual_b(prec, res, r, Ar, vs, n, nrhs, st);
     for (int it = 0; it < nu; ++it) {
       Dr(Ar, res);
       blas_cdot_norm_b(prec, Ar, res, vs, n, nrhs, c.red.outb(c.red.dres(), 3), st);
+      if (z64 && it + 1 == nu) {
+        spinor_mr_last(prec, z64, c.red.dres(), 3, e, res, Vh, nrhs, st);
+        return;
+      }
       blas_mr_update_b(prec, c.red.dres(), 3, e, res, Ar, vs, n, nrhs, st);
     }
   }
@@ -1281,20 +1297,14 @@ struct MGSolver {
     const size_t ne = op.neven(), na = op.nall(), cs = op.csize();
     const size_t nan = (size_t)Cn.cg.V * Cn.cg.n;
     const void* P = cp == WCMG_F64 ? T.v64.p : T.v32.p;
-    for (int i = 0; i < nrhs; ++i) {
-      const size_t o = (size_t)i * na * cs;
-      blas_copy(cp, (char*)V.rfull.p + o, (const char*)r + o, ne, st);
-      blas_zero(cp, (char*)V.rfull.p + o + ne * cs, na - ne, st);
-    }
+    blas_copy_b(cp, V.rfull.p, r, na, ne, nrhs, st);
+    blas_zero_b(cp, (char*)V.rfull.p + ne * cs, na, na - ne, nrhs, st);
     launch_ctr_restrict(cp, W.cb.p, Cn.cg.n, nan, V.rfull.p, na, P, T.vstride(), T.members.as<int>(), Cn.cg.V,
                         T.bg.bvol, C.cg.n, T.nvec, nrhs, st);
     coarse_solve_b(li + 1, W.cc.p, W.cb.p, nrhs);
     launch_ctr_prolong(cp, V.e.p, na, W.cc.p, nan, P, T.vstride(), T.blk.as<int>(), C.cg.V, C.cg.n, T.nvec, nrhs, st);
     mr_smooth_b([&](void* o, const void* i) { op.Dr(o, i, nrhs); }, cp, V.e.p, r, V.res.p, V.Ar.p, ne, na, nrhs);
-    for (int i = 0; i < nrhs; ++i) {
-      const size_t o = (size_t)i * na * cs;
-      blas_copy(cp, (char*)z + o, (const char*)V.e.p + o, ne, st);
-    }
+    blas_copy_b(cp, z, V.e.p, na, ne, nrhs, st);
   }
 
   // batched K(r_e) on nrhs FP64 even halves stored back to back
@@ -1304,7 +1314,7 @@ struct MGSolver {
     hipStream_t st = c.st;
     FineOp op{&c, &L.F, sp, &fwork, st, fprec};
     const size_t n = (size_t)12 * g.Vh;
-    const size_t h64 = spinor_bytes(WCMG_F64, g.Vh), hs = spinor_bytes(sp, g.Vh);
+    const size_t hs = spinor_bytes(sp, g.Vh);
     CoarseLevel& C = *L.levels[0];
     Level& V = lv[0];
     const size_t na = (size_t)C.cg.V * C.cg.n, cs = cp == WCMG_F64 ? 16 : 8;
@@ -1312,9 +1322,8 @@ struct MGSolver {
     fine_restrict(V.cb.p, na * cs, r_bl.p, hs, nrhs);
     coarse_solve_b(0, V.cc.p, V.cb.p, nrhs);
     fine_prolong(e_s.p, hs, V.cc.p, na * cs, nrhs);
-    mr_smooth_b([&](void* o, const void* i) { op.Dr(o, i, nrhs); }, sp, e_s.p, r_s.p, res_s.p, Ar_s.p, n, n, nrhs);
-    for (int i = 0; i < nrhs; ++i)
-      spinor_convert(WCMG_F64, (char*)z64 + i * h64, sp, (char*)e_s.p + i * hs, g.Vh, st);
+    mr_smooth_b([&](void* o, const void* i) { op.Dr(o, i, nrhs); }, sp, e_s.p, r_s.p, res_s.p, Ar_s.p, n, n, nrhs,
+                z64);
     ++calls;
   }
 };
