@@ -7,8 +7,9 @@
 // thread loads 16 bytes of eight vectors (padding slots read y again) before
 // the first of them is used, where a loop with a test per vector waits for
 // every load in turn.  Setup on 16^3x32 (FP32, 1.57 M complex, GCR(30), mean
-// over a cycle): multi-dot 77 -> 47 us, step 73 -> 44 us; outer GCR
-// (FP64, 0.79 M complex, mean over 17 steps) 52 -> 32 us, 38 -> 29 us.
+// over a cycle): multi-dot 77 -> 47 us, step 73 -> 44 us a step, and in pairs
+// of steps 49 and 46 us a pair; outer GCR (FP64, 0.79 M complex, mean over 17
+// steps) 52 -> 32 us, 38 -> 29 us.
 //
 // Sums accumulate in double in a fixed order: per thread, per wavefront, per
 // block, then over the blocks by the last one to arrive, so results are
@@ -64,44 +65,52 @@ struct Pack<float, 2> {
   }
 };
 
-// res[2j..2j+1] = <v_j, y>.  Workgroups of one chunk of elements and the
-// ng groups of kGroup vectors are numbered so that they run together on one
+// res[2j..2j+1] = <v_j, y>; PAIR: res[4j..4j+3] = <v_j, y>, <v_j, y2>.
+// Workgroups of one chunk of elements and the ng groups of kGroup vectors are numbered so that they run together on one
 // XCD (y is then read once from memory and found in that XCD's L2).
-template <typename T, int W>
-__global__ void __launch_bounds__(kThreads) k_multi_cdot(VecList m, int k, int ng, int nc, const void* y, size_t vs,
-                                                         size_t n, RedB o) {
+template <typename T, int W, bool PAIR = false>
+__global__ void __launch_bounds__(kThreads) k_multi_cdot(VecList m, int k, int ng, int nc, const void* y,
+                                                         const void* y2, size_t vs, size_t n, RedB o) {
   using P = Pack<T, W>;
   using V = typename P::V;
+  constexpr int NV = PAIR ? 4 : 2;
   const int t = blockIdx.x >> 3, g = t % ng, chunk = (t / ng) * 8 + (blockIdx.x & 7);
   const int j0 = g * kGroup, kb = min(kGroup, k - j0);
   const size_t ro = (size_t)blockIdx.y * vs * sizeof(typename C2<T>::V), nv = n / W;
   const V* yp = reinterpret_cast<const V*>(reinterpret_cast<const char*>(y) + ro);
+  const V* yp2 = reinterpret_cast<const V*>(reinterpret_cast<const char*>(PAIR ? y2 : y) + ro);
   const V* vp[kGroup];
 #pragma unroll
   for (int j = 0; j < kGroup; ++j)
     vp[j] = j < kb ? reinterpret_cast<const V*>(reinterpret_cast<const char*>(m.v[j0 + j]) + ro) : yp;
-  double s[2 * kGroup];
+  double s[NV * kGroup];
 #pragma unroll
-  for (int j = 0; j < 2 * kGroup; ++j) s[j] = 0.0;
+  for (int j = 0; j < NV * kGroup; ++j) s[j] = 0.0;
   for (size_t i = (size_t)chunk * kThreads + threadIdx.x; i < nv; i += (size_t)nc * kThreads) {
     const V yv = yp[i];
+    V yv2 = yv;
+    if constexpr (PAIR) yv2 = yp2[i];
     V q[kGroup];
 #pragma unroll
     for (int j = 0; j < kGroup; ++j) q[j] = vp[j][i];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const cpx<double> b = P::get(yv, w);
+      const cpx<double> b = P::get(yv, w), b2 = P::get(yv2, w);
 #pragma unroll
       for (int j = 0; j < kGroup; ++j) {
         const cpx<double> a = P::get(q[j], w);
-        s[2 * j] = fma(a.r, b.r, fma(a.i, b.i, s[2 * j]));
-        s[2 * j + 1] = fma(a.r, b.i, fma(-a.i, b.r, s[2 * j + 1]));
+        s[NV * j] = fma(a.r, b.r, fma(a.i, b.i, s[NV * j]));
+        s[NV * j + 1] = fma(a.r, b.i, fma(-a.i, b.r, s[NV * j + 1]));
+        if constexpr (PAIR) {
+          s[NV * j + 2] = fma(a.r, b2.r, fma(a.i, b2.i, s[NV * j + 2]));
+          s[NV * j + 3] = fma(a.r, b2.i, fma(-a.i, b2.r, s[NV * j + 3]));
+        }
       }
     }
   }
   const int row = blockIdx.y * ng + g;
-  block_reduce_row<2 * kGroup>(s, o.part + (size_t)row * nc * (2 * kGroup), o.counter + row * kCounterRow, nc, chunk,
-                               o.res + (size_t)blockIdx.y * o.rs + 2 * j0, nullptr, 2 * kb);
+  block_reduce_row<NV * kGroup>(s, o.part + (size_t)row * nc * (NV * kGroup), o.counter + row * kCounterRow, nc,
+                                chunk, o.res + (size_t)blockIdx.y * o.rs + NV * j0, nullptr, NV * kb);
 }
 
 // acc -= sum_j c_j v_j (SUB) or += at pack index i; c padded with zeros to a multiple of kGroup
@@ -206,6 +215,130 @@ __global__ void __launch_bounds__(kThreads) k_gcr_step(VecList m, int k, void* y
   }
   block_reduce_row<1>(s, o.part + (size_t)blockIdx.y * gridDim.x, o.counter + blockIdx.y * kCounterRow, gridDim.x,
                       blockIdx.x, o.res + (size_t)blockIdx.y * o.rs, nullptr, 1);
+}
+
+// Two GCR steps after one multi-dot with a pair: y1 = A z_k (which is the raw
+// direction z_k+1 and stays), y2 = A y1, and beta[4j..] = {<v_j, y1>, <v_j, y2>}
+// of v = {q_0 .. q_k-1, y1, y2, r}.  q_k = y1 - sum_j b1_j q_j,
+// q_k+1 = y2 - sum_j b2_j q_j - g q_k, rout = rin - alpha1 q_k - alpha2 q_k+1;
+// with <q_j, r> = 0 and q_k orthogonal to the q_j
+//   <q_k, y2> = <y1, y2> - sum_j conj(b1_j) <q_j, y2>,   <q_k+1, r> = <y2, r> - conj(g) <q_k, r>.
+// The span of {r, A r} is that of two steps (r after a step is r - alpha A r),
+// so a pair costs the basis two reads instead of four.  A y2 whose part outside
+// the basis is lost in rounding (1e-10 of its square) adds no direction.
+template <typename T, int W>
+__global__ void __launch_bounds__(kThreads) k_gcr_step_pair(VecList m, int k, const void* y1, void* q1, void* y2,
+                                                            const void* rin, void* rout, size_t n, const double* be,
+                                                            double* q4, double* cj1, double* cj2) {
+  using P = Pack<T, W>;
+  using V = typename P::V;
+  __shared__ double2 c1[kVecs + kGroup], c2[kVecs + kGroup];
+  __shared__ double t1[kVecs], t2[kVecs], gr[kVecs], gi[kVecs];
+  for (int j = threadIdx.x; j < k + kGroup; j += kThreads) {
+    const double d = j < k ? q4[4 * j] : 0.0;
+    double2 u = make_double2(0.0, 0.0), v = u;
+    double a = 0.0, b = 0.0, x = 0.0, z = 0.0;
+    if (d > 0.0) {
+      const double* e = be + 4 * j;
+      u = make_double2(e[0] / d, e[1] / d);
+      v = make_double2(e[2] / d, e[3] / d);
+      a = (e[0] * e[0] + e[1] * e[1]) / d;
+      b = (e[2] * e[2] + e[3] * e[3]) / d;
+      x = u.x * e[2] + u.y * e[3];
+      z = u.x * e[3] - u.y * e[2];
+    }
+    c1[j] = u;
+    c2[j] = v;
+    if (j < k) {
+      t1[j] = a;
+      t2[j] = b;
+      gr[j] = x;
+      gi[j] = z;
+    }
+  }
+  __syncthreads();
+  const double* e1 = be + 4 * k;  // <y1, y1>, <y1, y2>
+  const double* e2 = e1 + 4;      // <y2, y1>, <y2, y2>
+  const double* e3 = e2 + 4;      // <r, y1>, <r, y2>
+  double qq1 = e1[0], qq2 = e2[2];
+  cpx<double> g = mk(e1[2], e1[3]);
+  for (int j = 0; j < k; ++j) {
+    qq1 -= t1[j];
+    qq2 -= t2[j];
+    g.r -= gr[j];
+    g.i -= gi[j];
+  }
+  const cpx<double> r1 = mk(e3[0], -e3[1]);
+  cpx<double> alpha1 = mk(0.0, 0.0), alpha2 = alpha1;
+  if (qq1 > 0.0) {
+    alpha1 = mk(r1.r / qq1, r1.i / qq1);
+    qq2 -= (g.r * g.r + g.i * g.i) / qq1;
+    g = mk(g.r / qq1, g.i / qq1);
+  } else {
+    g = mk(0.0, 0.0);
+  }
+  const cpx<double> r2 = mk(e3[2] - (g.r * r1.r + g.i * r1.i), -e3[3] - (g.r * r1.i - g.i * r1.r));
+  if (!(qq2 > 1e-10 * e2[2])) qq2 = 0.0;
+  if (qq2 > 0.0) alpha2 = mk(r2.r / qq2, r2.i / qq2);
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      q4[4 * k] = qq1;
+      q4[4 * k + 1] = r1.r;
+      q4[4 * k + 2] = r1.i;
+      q4[4 * k + 4] = qq2;
+      q4[4 * k + 5] = r2.r;
+      q4[4 * k + 6] = r2.i;
+      cj2[2 * k] = g.r;
+      cj2[2 * k + 1] = g.i;
+    }
+    for (int j = threadIdx.x; j < k; j += kThreads) {
+      cj1[2 * j] = c1[j].x;
+      cj1[2 * j + 1] = c1[j].y;
+      cj2[2 * j] = c2[j].x;
+      cj2[2 * j + 1] = c2[j].y;
+    }
+  }
+  const size_t nv = n / W;
+  const V* y1p = reinterpret_cast<const V*>(y1);
+  V* q1p = reinterpret_cast<V*>(q1);
+  V* y2p = reinterpret_cast<V*>(y2);
+  const V* ip = reinterpret_cast<const V*>(rin);
+  V* op = reinterpret_cast<V*>(rout);
+  for (size_t l = (size_t)blockIdx.x * kThreads + threadIdx.x; l < nv; l += (size_t)gridDim.x * kThreads) {
+    const size_t i = nv - 1 - l;
+    V v1 = y1p[i], v2 = y2p[i], rv = ip[i];
+    cpx<double> a1[W], a2[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      a1[w] = P::get(v1, w);
+      a2[w] = P::get(v2, w);
+    }
+    for (int j0 = 0; j0 < k; j0 += kGroup) {
+      V q[kGroup];
+#pragma unroll
+      for (int j = 0; j < kGroup; ++j) q[j] = reinterpret_cast<const V*>(j0 + j < k ? m.v[j0 + j] : y1)[i];
+#pragma unroll
+      for (int j = 0; j < kGroup; ++j) {
+        const double2 u = c1[j0 + j], v = c2[j0 + j];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          const cpx<double> qv = P::get(q[j], w);
+          cfma(a1[w], mk(-u.x, -u.y), qv);
+          cfma(a2[w], mk(-v.x, -v.y), qv);
+        }
+      }
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      P::set(v1, w, a1[w]);
+      const cpx<double> s1 = P::get(v1, w);  // as stored
+      P::set(v2, w, a2[w] - g * s1);
+      P::set(rv, w, P::get(rv, w) - alpha1 * s1 - alpha2 * P::get(v2, w));
+    }
+    q1p[i] = v1;
+    y2p[i] = v2;
+    op[i] = rv;
+  }
 }
 
 // x += sum_j c_j v_j, c from the device (row r at coef + r cs) or the launch's arguments
@@ -333,13 +466,44 @@ void blas_multi_cdot_b(int prec, const void* const* v, int k, const void* y, siz
     nc = std::min<size_t>(nc, std::max<size_t>(4096 / ((size_t)ng * nrhs), 8));
     nc = (nc + 7) / 8 * 8;
     const RedB oo{o.res + 2 * j0, o.rs, o.part, o.counter};
-    DISPATCH_W(prec, wide, k_multi_cdot, dim3((unsigned)(nc * ng), nrhs), m, kk, ng, (int)nc, y, vs, n, oo);
+    DISPATCH_W(prec, wide, k_multi_cdot, dim3((unsigned)(nc * ng), nrhs), m, kk, ng, (int)nc, y, nullptr, vs, n,
+               oo);
   }
 }
 
 void blas_multi_cdot(int prec, const void* const* v, int k, const void* y, size_t n, const RedOut& o,
                      hipStream_t st) {
   blas_multi_cdot_b(prec, v, k, y, 0, n, 1, RedB{o.res, 0, o.partial, o.counter}, st);
+}
+
+void blas_multi_cdot_pair(int prec, const void* const* v, int k, const void* y1, const void* y2, size_t n,
+                          const RedOut& o, hipStream_t st) {
+  const int ng = (k + kGroup - 1) / kGroup;
+  const VecList m = vec_list(v, k);
+  const bool wide = wide_ok(v, k, y1, y2, nullptr, 0, n, 1);
+  const size_t nv = packs(prec, wide, n);
+  // as blas_multi_cdot_b, with the partials of twice the values in the same space
+  size_t nc = (std::min<size_t>((nv + kThreads - 1) / kThreads, kDotChunks) + 7) / 8 * 8;
+  nc = std::min<size_t>(nc, kRedPartials / (4 * kGroup) / ng / 8 * 8);
+  const RedB oo{o.res, 0, o.partial, o.counter};
+  const dim3 grid((unsigned)(nc * ng)), block(kThreads);
+  if (prec == WCMG_F64)
+    hipLaunchKernelGGL((k_multi_cdot<double, 1, true>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, (size_t)0, n, oo);
+  else if (wide)
+    hipLaunchKernelGGL((k_multi_cdot<float, 2, true>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, (size_t)0, n, oo);
+  else
+    hipLaunchKernelGGL((k_multi_cdot<float, 1, true>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, (size_t)0, n, oo);
+  HIPCHK(hipGetLastError());
+}
+
+void blas_gcr_step_pair(int prec, const void* const* q, int k, const void* y1, void* q1, void* y2, const void* rin,
+                        void* rout, size_t n, const double* beta, double* qa, double* cj1, double* cj2,
+                        hipStream_t st) {
+  const VecList m = vec_list(q, k);
+  const void* ends[2] = {y2, rin};
+  const bool wide = wide_ok(q, k, y1, q1, rout, 0, n, 1) && wide_ok(ends, 2, nullptr, nullptr, nullptr, 0, n, 1);
+  const dim3 grid(rows_grid(packs(prec, wide, n), 1, 2048));
+  DISPATCH_W(prec, wide, k_gcr_step_pair, grid, m, k, y1, q1, y2, rin, rout, n, beta, qa, cj1, cj2);
 }
 
 void blas_gcr_step_b(int prec, const void* const* q, int k, void* y, const void* rin, void* rout, size_t vs, size_t n,
