@@ -173,11 +173,11 @@ __device__ __forceinline__ C3 madd(const C3& a, const C3& b) {
 // with products formed in place: the sum over both sides kept apart (four more
 // matrices alive) took 372 registers, one wavefront per SIMD and 316 us; loads
 // held behind what stands before them (fewer registers still) 390 us; 256
-// registers, two wavefronts, loads free within a square, 262 us.
+// registers, two wavefronts, loads free within a square, 264 us.
 // 48 products of 3x3 matrices a link (90 us of FP64 arithmetic at this size)
 // and the gather of 18 links and 24 Z of 72 bytes through L1 and L2 bound it.
 // 16^3x32, one pair of spinors: hop part 87 us and clover part 614 us as
-// launches of their own, 262 us now; the insertion 63 us, 29 us now.
+// launches of their own, 264 us now; the insertion 63 us, 29 us now.
 struct ForceLinks {
   const double2* gauge;
   const double* Z;
@@ -284,19 +284,23 @@ __global__ void __launch_bounds__(256, 2) k_link_force(double2* G, const double2
   const size_t yp = lex_of(f.g.L, cm);
   // spatial hops carry the coefficient hs (1 on isotropic lattices), the last time slice its phase
   const double ph = mu < 3 ? f.g.hs : (c[3] == f.g.L[3] - 1 ? f.g.t_bc : 1.0);
-  C3 acc;
+  C3 acc, cl;
+  if constexpr (CLOVER) {
+    // first, from zero: added to the hop part term by term it would be rounded at the sum's size
+#pragma unroll
+    for (int k = 0; k < 9; ++k) cl.m[k] = mk(0.0, 0.0);
+#pragma unroll 1
+    for (int k = 1; k < 4; ++k) {
+      const int nu = (mu + k) & 3;
+      clover_force_side<true>(f, c, cm, mu, nu, cl);
+      clover_force_side<false>(f, c, cm, mu, nu, cl);
+    }
+  }
   if (mu == 0) hop_force_mu<0>(x, lam, nrhs, V, y, yp, ph, acc.m);
   else if (mu == 1) hop_force_mu<1>(x, lam, nrhs, V, y, yp, ph, acc.m);
   else if (mu == 2) hop_force_mu<2>(x, lam, nrhs, V, y, yp, ph, acc.m);
   else hop_force_mu<3>(x, lam, nrhs, V, y, yp, ph, acc.m);
-  if constexpr (CLOVER) {
-#pragma unroll 1
-    for (int k = 1; k < 4; ++k) {
-      const int nu = (mu + k) & 3;
-      clover_force_side<true>(f, c, cm, mu, nu, acc);
-      clover_force_side<false>(f, c, cm, mu, nu, acc);
-    }
-  }
+  if constexpr (CLOVER) acc = madd(acc, cl);
   double2* o = G + ((size_t)y * 4 + mu) * 9;
 #pragma unroll
   for (int k = 0; k < 9; ++k) o[k] = make_double2(acc.m[k].r, acc.m[k].i);
