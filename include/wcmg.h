@@ -269,7 +269,9 @@ int wcmg_get_coarse(void* ctx, int lat, int level, void* Y, int on_device);
  * D^dag): every lattice of the context (at most 4, of any volumes), buffers
  * holding nrhs spinors of each lattice, concatenated in lattice order; for
  * each right-hand side every kernel is one launch over all lattices (a work
- * list of per-lattice block ranges).  Asynchronous. */
+ * list of per-lattice block ranges).  out == in is refused; with lat >= 0 the
+ * two may overlap otherwise (the input then counts as read first, from a copy
+ * in the context's scratch).  Asynchronous. */
 int wcmg_apply_D(void* ctx, int lat, int op, int prec, void* out, const void* in, int nrhs);
 int wcmg_apply_Ddag(void* ctx, int lat, int op, int prec, void* out, const void* in, int nrhs);
 
@@ -277,7 +279,8 @@ int wcmg_apply_Ddag(void* ctx, int lat, int op, int prec, void* out, const void*
  * restrict: coarse = R fine = P^dag gamma5 fine;  prolong: fine = P coarse.
  * Level 0 fine vectors are canonical spinors (both parities); coarse
  * vectors of level l >= 1 are complex128 [Vc][2 Nv] in lexicographic
- * coarse-site order.  prec (F64/F32 on coarse levels) is the arithmetic. */
+ * coarse-site order.  prec (F64/F32 on coarse levels) is the arithmetic.
+ * Between level 0 and 1 the output may overlap the input (as in the applies). */
 int wcmg_restrict(void* ctx, int lat, int level, int prec, void* coarse_out, const void* fine_in, int nrhs);
 int wcmg_prolong(void* ctx, int lat, int level, int prec, void* fine_out, const void* coarse_in, int nrhs);
 

@@ -142,6 +142,18 @@ int check_dev(Ctx* c, const void* p, size_t bytes, const char* what) {
     if (int r_ = check_dev((c), (p), (bytes), (what))) return r_; \
   } while (0)
 
+// Kernels that take the caller's vectors in place read the input while others
+// write the output.  An input that shares memory with the output is read from a
+// copy instead, so that all of it is read before any of it is overwritten.
+const void* apart(Ctx& c, const void* in, size_t in_bytes, const void* out, size_t out_bytes) {
+  const char* i = (const char*)in;
+  const char* o = (const char*)out;
+  if (i + in_bytes <= o || o + out_bytes <= i) return in;
+  void* d = c.scratch_buf(56, in_bytes);
+  HIPCHK(hipMemcpyAsync(d, in, in_bytes, hipMemcpyDeviceToDevice, c.st));
+  return d;
+}
+
 int check_lat(Ctx* c, int lat) {
   if (!c) return set_err(WCMG_EINVAL, "null context");
   if (lat < 0 || lat >= (int)c->lats.size()) return set_err(WCMG_EINVAL, "lattice index out of range");
@@ -729,7 +741,8 @@ static int apply_common(void* ctx, int lat, int op, int prec, void* out, const v
   return guarded([&] {
     // all right-hand sides go through each kernel in one batched launch
     FineOp fo{c, &L.F, prec, &c->fw[prec], c->st};
-    fo.apply(op, dag, out, in, nrhs);
+    const size_t bytes = (size_t)nrhs * L.F.g.V * 12 * 16;
+    fo.apply(op, dag, out, apart(*c, in, bytes, out, bytes), nrhs);
   });
 }
 
@@ -794,6 +807,7 @@ static void transfer_fine(Ctx* c, LatticeState& L, int prec, int nrhs, void* out
   const void* vecs = prec == WCMG_F64 ? T.v64.p : T.v32.p;
   const bool half = prec == WCMG_F16;
   const size_t hb = spinor_bytes(WCMG_F16, g.Vh);
+  in = apart(*c, in, nrhs * (to_coarse ? one : cone), out, nrhs * (to_coarse ? cone : one));
   char* fe = nullptr;
   char* fo = nullptr;
   char* rounded = nullptr;
