@@ -720,6 +720,10 @@ static int apply_all_lattices(Ctx* c, int op, int prec, void* out, const void* i
   });
 }
 
+// right-hand sides of an apply that share a launch: some kernels count them in
+// the grid's second extent, which ends at 65535
+constexpr int kMaxApply = 32768;
+
 static int apply_common(void* ctx, int lat, int op, int prec, void* out, const void* in, int nrhs, bool dag) {
   Ctx* c = as_ctx(ctx);
   if (lat == -1 && c) {
@@ -741,8 +745,10 @@ static int apply_common(void* ctx, int lat, int op, int prec, void* out, const v
   return guarded([&] {
     // all right-hand sides go through each kernel in one batched launch
     FineOp fo{c, &L.F, prec, &c->fw[prec], c->st};
-    const size_t bytes = (size_t)nrhs * L.F.g.V * 12 * 16;
-    fo.apply(op, dag, out, apart(*c, in, bytes, out, bytes), nrhs);
+    const size_t one = (size_t)L.F.g.V * 12 * 16;
+    in = apart(*c, in, nrhs * one, out, nrhs * one);
+    for (int r0 = 0; r0 < nrhs; r0 += kMaxApply)
+      fo.apply(op, dag, (char*)out + r0 * one, (const char*)in + r0 * one, std::min(kMaxApply, nrhs - r0));
   });
 }
 
