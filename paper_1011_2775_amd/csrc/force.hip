@@ -80,6 +80,38 @@ __device__ __forceinline__ void hop_force_mu(const double2* x, const double2* la
   for (int k = 0; k < 9; ++k) acc[k] = (0.5 * ph) * acc[k];
 }
 
+template <int MU>
+__device__ __forceinline__ void hop_force_store(double2* G, const double2* x, const double2* lam, int nrhs, size_t V,
+                                                size_t y, size_t yp, double ph) {
+  cpx<double> acc[9];
+  hop_force_mu<MU>(x, lam, nrhs, V, y, yp, ph, acc);
+  double2* o = G + (y * 4 + MU) * 9;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) o[k] = make_double2(acc[k].r, acc[k].i);
+}
+
+// The hop part of all four links of a site by one thread, which reads the site's
+// own spinors once.  Bound by the gather of four neighbours a pair of spinors.
+// k_link_force<false>, a wavefront per direction, reads the site's spinors four
+// times: three pairs at 16^3x32 190 us here and 234 us there, at 32^2x8^2 80 and
+// 116 us.
+__global__ void __launch_bounds__(kT) k_hop_force(double2* G, const double2* x, const double2* lam, int nrhs,
+                                                  DGeom g) {
+  const int y = blockIdx.x * blockDim.x + threadIdx.x, V = 2 * g.Vh;
+  if (y >= V) return;
+  int c[4], n[4];
+  coords_of(g.L, y, c);
+  // spatial hops carry the coefficient hs (1 on isotropic lattices), the last time slice its phase
+  shift(g.L, c, 0, 1, n);
+  hop_force_store<0>(G, x, lam, nrhs, V, y, lex_of(g.L, n), g.hs);
+  shift(g.L, c, 1, 1, n);
+  hop_force_store<1>(G, x, lam, nrhs, V, y, lex_of(g.L, n), g.hs);
+  shift(g.L, c, 2, 1, n);
+  hop_force_store<2>(G, x, lam, nrhs, V, y, lex_of(g.L, n), g.hs);
+  shift(g.L, c, 3, 1, n);
+  hop_force_store<3>(G, x, lam, nrhs, V, y, lex_of(g.L, n), c[3] == g.L[3] - 1 ? g.t_bc : 1.0);
+}
+
 // site of place t (parity p = t / Vh, checkerboard index t mod Vh): coordinates and lexicographic index
 __device__ __forceinline__ int force_site(const DGeom& g, int t, int c[4]) {
   const int p = t >= g.Vh, i = t - p * g.Vh;
@@ -305,6 +337,12 @@ __global__ void __launch_bounds__(256, 2) k_link_force(double2* G, const double2
 #pragma unroll
   for (int k = 0; k < 9; ++k) o[k] = make_double2(acc.m[k].r, acc.m[k].i);
 }
+
+// Sites from which the hop part alone is done by a thread a site: a wavefront for each of the 256
+// compute units.  Below, a wavefront per direction finds idle units (three pairs at 12288 sites 30.5
+// against 31.7 us, twelve 112 against 134); above, its workgroups come in a second round (three pairs
+// at 16800 sites 46 against 39 us).
+constexpr int kSiteThreads = 64 * 256;
 }  // namespace
 
 void force_compute(void* G, const void* x, const void* lam, int nrhs, const void* gauge64, const Geom& g,
@@ -312,8 +350,13 @@ void force_compute(void* G, const void* x, const void* lam, int nrhs, const void
   ForceLinks f{reinterpret_cast<const double2*>(gauge64), reinterpret_cast<const double*>(zbuf), dgeom(g)};
   const double2* xs = reinterpret_cast<const double2*>(x);
   const double2* ls = reinterpret_cast<const double2*>(lam);
+  const dim3 gz((g.V + kT - 1) / kT);
+  if (!cc && g.V >= kSiteThreads) {
+    hipLaunchKernelGGL(k_hop_force, gz, dim3(kT), 0, st, reinterpret_cast<double2*>(G), xs, ls, nrhs, f.g);
+    HIPCHK(hipGetLastError());
+    return;
+  }
   if (cc) {
-    const dim3 gz((g.V + kT - 1) / kT);
     if (nrhs == 1)
       hipLaunchKernelGGL(k_clover_insertion<true>, gz, dim3(kT), 0, st, reinterpret_cast<double*>(zbuf), xs, ls, nrhs,
                          *cc, f.g);
