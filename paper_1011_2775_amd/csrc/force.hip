@@ -60,21 +60,27 @@ __device__ __forceinline__ void hop_force_mu(const double2* x, const double2* la
     one_pm_gamma<MU, false>(v, w);
     load12(lam, off + y, l);
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+      for (int b = 0; b < 3; ++b) {
+        cpx<double> t = mk(0.0, 0.0);
 #pragma unroll
-        for (int b = 0; b < 3; ++b) cfmac(acc[a * 3 + b], w[s * 3 + b], l[s * 3 + a]);
+        for (int s = 0; s < 4; ++s) cfmac(t, w[s * 3 + b], l[s * 3 + a]);
+        acc[a * 3 + b] = acc[a * 3 + b] + t;
+      }
     // phi_s lambda(y+mu)_s^dag,  phi = (1 + gamma) x(y)
     load12(x, off + y, v);
     one_pm_gamma<MU, true>(v, w);
     load12(lam, off + yp, l);
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
+      for (int b = 0; b < 3; ++b) {
+        cpx<double> t = mk(0.0, 0.0);
 #pragma unroll
-        for (int b = 0; b < 3; ++b) cfmac(acc[a * 3 + b], l[s * 3 + b], w[s * 3 + a]);
+        for (int s = 0; s < 4; ++s) cfmac(t, l[s * 3 + b], w[s * 3 + a]);
+        acc[a * 3 + b] = acc[a * 3 + b] + t;
+      }
   }
 #pragma unroll
   for (int k = 0; k < 9; ++k) acc[k] = (0.5 * ph) * acc[k];
@@ -235,16 +241,22 @@ __device__ __forceinline__ C3 load_zc(const ForceLinks& f, int pl, const int c[4
   return m;
 }
 
-// acc += s A B
+// acc += s A B, each row of the product from zero: terms added to acc one by one would be rounded
+// at the size of the whole sum
 __device__ __forceinline__ void mul_add(C3& acc, double s, const C3& A, const C3& B) {
 #pragma unroll
-  for (int i = 0; i < 3; ++i)
+  for (int i = 0; i < 3; ++i) {
+    cpx<double> t[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const cpx<double> a = s * A.m[i * 3 + k];
+    for (int j = 0; j < 3; ++j) t[j] = mk(0.0, 0.0);
 #pragma unroll
-      for (int j = 0; j < 3; ++j) cfma(acc.m[i * 3 + j], a, B.m[k * 3 + j]);
-    }
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) cfma(t[j], A.m[i * 3 + k], B.m[k * 3 + j]);
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      acc.m[i * 3 + j] = mk(fma(s, t[j].r, acc.m[i * 3 + j].r), fma(s, t[j].i, acc.m[i * 3 + j].i));
+  }
 }
 // B <- A B, column by column; B <- B A, row by row
 __device__ __forceinline__ void left_mul(const C3& A, C3& B) {
