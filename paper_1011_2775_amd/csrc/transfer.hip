@@ -206,9 +206,13 @@ __device__ __forceinline__ const void* fine_base(const RestrictArgs& a, const vo
 // of the vectors.  16^3x32, Nv 24: FP64, both parities, from the canonical layout
 // 435 -> 120 us (5.2 TB/s, a large copy's rate); FP32 even half with FP16 vectors
 // (the cycle) 35 -> 26 us.
+// FP64 sums: a lane's 24 units added in a row had an error of 2.7e-16 against
+// 1.8e-16 of a thread per site; three units at a time into a sum of two words
+// 1.6e-16, at the same speed.
 constexpr int kRV = 8;
 
-template <typename VT, bool CANON>
+// PARTS: FP64 results from blocks of at least 192 units, summed in parts
+template <typename VT, bool CANON, bool PARTS>
 __global__ void __launch_bounds__(128) k_restrict(RestrictArgs a) {
   using X = VecUnit<VT>;
   using C = typename X::C;
@@ -223,17 +227,16 @@ __global__ void __launch_bounds__(128) k_restrict(RestrictArgs a) {
     fill_offsets<CANON, E>(off, a, b, U);
     __syncthreads();
   }
-  double acc[2 * kRV];
+  double acc[2 * kRV], low[2 * kRV];
 #pragma unroll
-  for (int j = 0; j < 2 * kRV; ++j) acc[j] = 0.0;
+  for (int j = 0; j < 2 * kRV; ++j) acc[j] = low[j] = 0.0;
   for (int ip = 0; ip < a.np; ++ip) {
     const void* in = fine_base<CANON, E>(a, a.in[0], b, s);
     const L* v[kRV];
 #pragma unroll
     for (int j = 0; j < kRV; ++j)
       v[j] = reinterpret_cast<const L*>(a.vecs) + vec_at(a.bg, min(k0 + j, a.nvec - 1), a.p0 + ip, b, s) / (E * G);
-#pragma unroll 3
-    for (int u = lane; u < U / G; u += 64) {
+    auto add = [&](int u, double (&sum)[2 * kRV]) {
       FineIn<C, E, CANON> w[G];
 #pragma unroll
       for (int h = 0; h < G; ++h) {
@@ -256,13 +259,34 @@ __global__ void __launch_bounds__(128) k_restrict(RestrictArgs a) {
 #pragma unroll
           for (int e = 0; e < E; ++e) {
             const double wr = (double)wv[e].r, wi = (double)wv[e].i, vr = (double)vv[e].r, vi = (double)vv[e].i;
-            acc[2 * j] = fma(vr, wr, fma(vi, wi, acc[2 * j]));
-            acc[2 * j + 1] = fma(vr, wi, fma(-vi, wr, acc[2 * j + 1]));
+            sum[2 * j] = fma(vr, wr, fma(vi, wi, sum[2 * j]));
+            sum[2 * j + 1] = fma(vr, wi, fma(-vi, wr, sum[2 * j + 1]));
           }
         }
       }
-    }
+    };
+    int u = lane;
+    // three units from zero, added to a sum of two words: a lane's chain of roundings stays short
+    if constexpr (PARTS)
+      for (; u + 128 < U; u += 192) {
+        double part[2 * kRV];
+#pragma unroll
+        for (int j = 0; j < 2 * kRV; ++j) part[j] = 0.0;
+#pragma unroll
+        for (int h = 0; h < 3; ++h) add(u + 64 * h, part);
+#pragma unroll
+        for (int j = 0; j < 2 * kRV; ++j) {
+          const double t = acc[j] + part[j], w = t - acc[j];
+          low[j] += (acc[j] - (t - w)) + (part[j] - w);
+          acc[j] = t;
+        }
+      }
+#pragma unroll 3
+    for (; u < U / G; u += 64) add(u, acc);
   }
+  if constexpr (PARTS)
+#pragma unroll
+    for (int j = 0; j < 2 * kRV; ++j) acc[j] = isfinite(low[j]) ? acc[j] + low[j] : acc[j];
   // after the exchange over lane bit m the lanes with the bit set hold the upper half of the values
 #pragma unroll
   for (int h = kRV, m = 32; h >= 1; h >>= 1, m >>= 1) {
@@ -297,10 +321,16 @@ __global__ void __launch_bounds__(128) k_restrict(RestrictArgs a) {
 // vectors 400 -> 86 us; nine FP64 inputs in the block layout (a column of the
 // coarse build) 3830 -> 237 us.  One input stays on k_restrict: there the tiles
 // are mostly padding (FP32 84 us against 117 us with two inputs).
+// FP64 sums: accumulated through the instructions, K / 4 roundings in a row,
+// they had an error of 9.3e-16 (blocks of 256 sites) where one vector had
+// 1.8e-16; the products of a step from zero, added to a sum of two words, have
+// 1.3e-16.  The second words take the registers of two wavefronts per SIMD with
+// two row and two column tiles, and the time stays (12 inputs, Nv 24: 291 and
+// 294 us).
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <typename VT, bool CANON, int MT, int NT>
-__global__ void __launch_bounds__(256, MT * NT <= 4 ? 4 : 2) k_restrict_mfma(RestrictArgs a) {
+__global__ void __launch_bounds__(256, MT * NT <= (sizeof(VT) == 8 ? 2 : 4) ? 4 : 2) k_restrict_mfma(RestrictArgs a) {
   using X = VecUnit<VT>;
   using C = typename X::C;
   using L = typename X::L;
@@ -314,12 +344,12 @@ __global__ void __launch_bounds__(256, MT * NT <= 4 ? 4 : 2) k_restrict_mfma(Res
   __syncthreads();
   // the wavefront's number in a scalar register: the loop's bounds are then scalar too
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), s = blockIdx.y;
-  const int q = lane >> 4, j = lane & 15;
+  const int q = lane >> 4, j = lane & 15, k0 = blockIdx.z * 16 * MT;
   const bool im = j & 1;
   const L* v[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
-    v[m] = reinterpret_cast<const L*>(a.vecs) + vec_at(a.bg, min(16 * m + j, a.nvec - 1), a.p0, b, s) / (E * G);
+    v[m] = reinterpret_cast<const L*>(a.vecs) + vec_at(a.bg, min(k0 + 16 * m + j, a.nvec - 1), a.p0, b, s) / (E * G);
   const int pstep = a.bg.Vc * 2 * U / G;  // loads from one parity to the other
   const void* w[NT];
 #pragma unroll
@@ -345,7 +375,7 @@ __global__ void __launch_bounds__(256, MT * NT <= 4 ? 4 : 2) k_restrict_mfma(Res
       for (int n = 0; n < NT; ++n) st.w[n][h].load(w[n], o);
     }
   };
-  auto multiply = [&](const Step& st) {
+  auto multiply = [&](const Step& st, d4 (&acc)[MT][NT]) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       // B fragments: the right-hand side, or -i times it in odd columns
@@ -389,16 +419,54 @@ __global__ void __launch_bounds__(256, MT * NT <= 4 ? 4 : 2) k_restrict_mfma(Res
     load(at(0), s0);
     load(at(1), s1);
     int i = 0;
-    for (; i + 3 <= steps; i += 3) {
+    auto three = [&](auto&& each) {
       load(at(i + 2), s2);
-      multiply(s0);
+      each(s0);
       load(at(i + 3), s0);
-      multiply(s1);
+      each(s1);
       load(at(i + 4), s1);
-      multiply(s2);
+      each(s2);
+      i += 3;
+    };
+    // FP64 results: the products of a step are summed from zero and added to a sum of two words
+    if constexpr (sizeof(VT) == 8) {
+      d4 low[MT][NT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) low[m][n] = (d4){0.0, 0.0, 0.0, 0.0};
+      auto exact_add = [&](const Step& st) {
+        d4 part[MT][NT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int n = 0; n < NT; ++n) part[m][n] = (d4){0.0, 0.0, 0.0, 0.0};
+        multiply(st, part);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const d4 t = acc[m][n] + part[m][n], v = t - acc[m][n];
+            low[m][n] += (acc[m][n] - (t - v)) + (part[m][n] - v);
+            acc[m][n] = t;
+          }
+      };
+      while (i + 3 <= steps) three(exact_add);
+      if (i < steps) exact_add(s0);
+      if (i + 1 < steps) exact_add(s1);
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)  // an infinite sum has no low word
+            acc[m][n][r] = isfinite(low[m][n][r]) ? acc[m][n][r] + low[m][n][r] : acc[m][n][r];
+    } else {
+      auto add = [&](const Step& st) { multiply(st, acc); };
+      while (i + 3 <= steps) three(add);
+      if (i < steps) add(s0);
+      if (i + 1 < steps) add(s1);
     }
-    if (i < steps) multiply(s0);
-    if (i + 1 < steps) multiply(s1);
   }
 #pragma unroll
   for (int m = 0; m < MT; ++m)
@@ -409,7 +477,7 @@ __global__ void __launch_bounds__(256, MT * NT <= 4 ? 4 : 2) k_restrict_mfma(Res
       __syncthreads();
       const int tid = threadIdx.x;
       const double sum = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-      const int k = 16 * m + 4 * wave + q, rhs = 8 * n + (j >> 1);
+      const int k = k0 + 16 * m + 4 * wave + q, rhs = 8 * n + (j >> 1);
       if (k < a.nvec && rhs < a.nin) put_coarse<C, CANON>(a, rhs, b, s * a.nvec + k, j & 1, s ? -sum : sum);
       __syncthreads();
     }
@@ -581,25 +649,36 @@ constexpr int kOrthoThreads = 512;
 __global__ void __launch_bounds__(kOrthoThreads) k_block_ortho(double2* vecs, int nvec, BlockGeom bg, int* flag) {
   extern __shared__ __align__(16) char shm[];
   __shared__ double2 cf[64];
-  __shared__ double nrm[kOrthoThreads / 64];
+  __shared__ double2 nrm[kOrthoThreads / 64];
   double2* v = reinterpret_cast<double2*>(shm);  // [2][half * 6]
   const int b = blockIdx.x, s = blockIdx.y, run = bg.bvol / 2 * 6, len = 2 * run;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const size_t pstep = vec_at(bg, 0, 1, 0, 0), kstep = 2 * pstep;
   double2* base = vecs + vec_at(bg, 0, 0, b, s);
   auto at = [&](int e) { return e < run ? (size_t)e : pstep + (e - run); };
-  // sum of squares of v over the workgroup (every thread gets it)
+  // sum of squares of v over the workgroup (every thread gets it), carried in two words: an error
+  // of a norm scales a whole vector and does not average out in a product with it
   auto norm2 = [&]() {
-    double t = 0.0;
-    for (int e = threadIdx.x; e < len; e += kOrthoThreads) t += v[e].x * v[e].x + v[e].y * v[e].y;
+#pragma clang fp contract(off)
+    double t = 0.0, low = 0.0;
+    auto add = [&](double p, double l) {
+      const double u = t + p, w = u - t;
+      low += ((t - (u - w)) + (p - w)) + l;
+      t = u;
+    };
+    for (int e = threadIdx.x; e < len; e += kOrthoThreads) {
+      const double x = v[e].x, y = v[e].y;
+      add(x * x, fma(x, x, -(x * x)));
+      add(y * y, fma(y, y, -(y * y)));
+    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
+    for (int off = 32; off > 0; off >>= 1) add(__shfl_xor(t, off), __shfl_xor(low, off));
     __syncthreads();
-    if (lane == 0) nrm[wave] = t;
+    if (lane == 0) nrm[wave] = make_double2(t, low);
     __syncthreads();
-    double r = 0.0;
-    for (int q = 0; q < kOrthoThreads / 64; ++q) r += nrm[q];
-    return r;
+    t = low = 0.0;
+    for (int q = 0; q < kOrthoThreads / 64; ++q) add(nrm[q].x, nrm[q].y);
+    return t + low;
   };
   for (int k = 0; k < nvec; ++k) {
     double2* vk = base + (size_t)k * kstep;
@@ -608,13 +687,21 @@ __global__ void __launch_bounds__(kOrthoThreads) k_block_ortho(double2* vecs, in
     for (int pass = 0; pass < 2 && k > 0; ++pass) {
       for (int j = wave; j < k; j += kOrthoThreads / 64) {
         const double2* qj = base + (size_t)j * kstep;
-        double sr = 0.0, si = 0.0;
-#pragma unroll 4
-        for (int e = lane; e < len; e += 64) {
+        double pr[4] = {0.0, 0.0, 0.0, 0.0}, pi[4] = {0.0, 0.0, 0.0, 0.0};
+        int e = lane;
+        for (; e + 192 < len; e += 256)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const double2 t = qj[at(e + 64 * u)], x = v[e + 64 * u];
+            pr[u] += t.x * x.x + t.y * x.y;
+            pi[u] += t.x * x.y - t.y * x.x;
+          }
+        for (; e < len; e += 64) {
           const double2 t = qj[at(e)], x = v[e];
-          sr += t.x * x.x + t.y * x.y;
-          si += t.x * x.y - t.y * x.x;
+          pr[0] += t.x * x.x + t.y * x.y;
+          pi[0] += t.x * x.y - t.y * x.x;
         }
+        double sr = (pr[0] + pr[1]) + (pr[2] + pr[3]), si = (pi[0] + pi[1]) + (pi[2] + pi[3]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
           sr += __shfl_xor(sr, off);
@@ -761,13 +848,16 @@ template <typename VT, bool CANON>
 void restrict_t(const RestrictArgs& a, hipStream_t st) {
   const size_t shm = (size_t)a.np * (a.bg.bvol / 2) * (6 / VecUnit<VT>::E) * sizeof(int);
   if (a.nin == 1) {
-    hipLaunchKernelGGL((k_restrict<VT, CANON>), dim3(xcd_grid(a.bg.Vc), transfer_tiles(a.nvec, kRV)), dim3(128),
-                       CANON ? shm : 0, st, a);
+    const dim3 g1(xcd_grid(a.bg.Vc), transfer_tiles(a.nvec, kRV));
+    if (sizeof(VT) == 8 && a.bg.bvol / 2 * 6 >= 192)
+      hipLaunchKernelGGL((k_restrict<VT, CANON, sizeof(VT) == 8>), g1, dim3(128), CANON ? shm : 0, st, a);
+    else
+      hipLaunchKernelGGL((k_restrict<VT, CANON, false>), g1, dim3(128), CANON ? shm : 0, st, a);
     HIPCHK(hipGetLastError());
     return;
   }
-  const dim3 grid(xcd_grid(a.bg.Vc), 2);
   const int mt = transfer_tiles(a.nvec, 16);
+  dim3 grid(xcd_grid(a.bg.Vc), 2);
 #define WCMG_RM(M)                                                                                    \
   do {                                                                                                \
     if (a.nin <= 8)                                                                                   \
@@ -775,10 +865,20 @@ void restrict_t(const RestrictArgs& a, hipStream_t st) {
     else                                                                                              \
       hipLaunchKernelGGL((k_restrict_mfma<VT, CANON, M, 2>), grid, dim3(256), shm, st, a);            \
   } while (0)
-  if (mt == 1) WCMG_RM(1);
-  else if (mt == 2) WCMG_RM(2);
-  else if (mt == 3) WCMG_RM(3);
-  else WCMG_RM(4);
+  if (mt == 1) {
+    WCMG_RM(1);
+  } else if (mt == 2) {
+    WCMG_RM(2);
+  } else if (mt == 3) {
+    WCMG_RM(3);
+  } else if (sizeof(VT) == 8 && a.nin > 8) {
+    // four row tiles, two column tiles and their low words exceed the registers (1550 us at 16^4, blocks
+    // of 1024 sites, 12 inputs): two rows each
+    grid.z = 2;
+    WCMG_RM(2);
+  } else {
+    WCMG_RM(4);
+  }
 #undef WCMG_RM
   HIPCHK(hipGetLastError());
 }
