@@ -65,45 +65,48 @@ struct Pack<float, 2> {
   }
 };
 
-// res[2j..2j+1] = <v_j, y>; PAIR: res[4j..4j+3] = <v_j, y>, <v_j, y2>.
+// res[2j..2j+1] = <v_j, y>; NY = 3: res[6j..6j+5] = <v_j, y>, <v_j, y2>, <v_j, y3>.
 // Workgroups of one chunk of elements and the ng groups of kGroup vectors are numbered so that they run together on one
 // XCD (y is then read once from memory and found in that XCD's L2).
-template <typename T, int W, bool PAIR = false>
-__global__ void __launch_bounds__(kThreads) k_multi_cdot(VecList m, int k, int ng, int nc, const void* y,
-                                                         const void* y2, size_t vs, size_t n, RedB o) {
+template <typename T, int W, int NY = 1>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, NY == 3 ? 2 : 8))) k_multi_cdot(VecList m, int k, int ng, int nc, const void* y,
+                                                         const void* y2, const void* y3, size_t vs, size_t n, RedB o) {
   using P = Pack<T, W>;
   using V = typename P::V;
-  constexpr int NV = PAIR ? 4 : 2;
+  constexpr int NV = 2 * NY;
   const int t = blockIdx.x >> 3, g = t % ng, chunk = (t / ng) * 8 + (blockIdx.x & 7);
   const int j0 = g * kGroup, kb = min(kGroup, k - j0);
   const size_t ro = (size_t)blockIdx.y * vs * sizeof(typename C2<T>::V), nv = n / W;
-  const V* yp = reinterpret_cast<const V*>(reinterpret_cast<const char*>(y) + ro);
-  const V* yp2 = reinterpret_cast<const V*>(reinterpret_cast<const char*>(PAIR ? y2 : y) + ro);
+  const void* ys[3] = {y, y2, y3};
+  const V* yp[NY];
+#pragma unroll
+  for (int c = 0; c < NY; ++c) yp[c] = reinterpret_cast<const V*>(reinterpret_cast<const char*>(ys[c]) + ro);
   const V* vp[kGroup];
 #pragma unroll
   for (int j = 0; j < kGroup; ++j)
-    vp[j] = j < kb ? reinterpret_cast<const V*>(reinterpret_cast<const char*>(m.v[j0 + j]) + ro) : yp;
+    vp[j] = j < kb ? reinterpret_cast<const V*>(reinterpret_cast<const char*>(m.v[j0 + j]) + ro) : yp[0];
   double s[NV * kGroup];
 #pragma unroll
   for (int j = 0; j < NV * kGroup; ++j) s[j] = 0.0;
   for (size_t i = (size_t)chunk * kThreads + threadIdx.x; i < nv; i += (size_t)nc * kThreads) {
-    const V yv = yp[i];
-    V yv2 = yv;
-    if constexpr (PAIR) yv2 = yp2[i];
-    V q[kGroup];
+    V yv[NY], q[kGroup];
+#pragma unroll
+    for (int c = 0; c < NY; ++c) yv[c] = yp[c][i];
 #pragma unroll
     for (int j = 0; j < kGroup; ++j) q[j] = vp[j][i];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const cpx<double> b = P::get(yv, w), b2 = P::get(yv2, w);
+      cpx<double> b[NY];
+#pragma unroll
+      for (int c = 0; c < NY; ++c) b[c] = P::get(yv[c], w);
 #pragma unroll
       for (int j = 0; j < kGroup; ++j) {
         const cpx<double> a = P::get(q[j], w);
-        s[NV * j] = fma(a.r, b.r, fma(a.i, b.i, s[NV * j]));
-        s[NV * j + 1] = fma(a.r, b.i, fma(-a.i, b.r, s[NV * j + 1]));
-        if constexpr (PAIR) {
-          s[NV * j + 2] = fma(a.r, b2.r, fma(a.i, b2.i, s[NV * j + 2]));
-          s[NV * j + 3] = fma(a.r, b2.i, fma(-a.i, b2.r, s[NV * j + 3]));
+#pragma unroll
+        for (int c = 0; c < NY; ++c) {
+          double* d = s + NV * j + 2 * c;
+          d[0] = fma(a.r, b[c].r, fma(a.i, b[c].i, d[0]));
+          d[1] = fma(a.r, b[c].i, fma(-a.i, b[c].r, d[1]));
         }
       }
     }
@@ -218,11 +221,17 @@ __global__ void __launch_bounds__(kThreads) k_gcr_step(VecList m, int k, void* y
 }
 
 // Two GCR steps after one multi-dot with a pair: y1 = A z_k (which is the raw
-// direction z_k+1 and stays), y2 = A y1, and beta[4j..] = {<v_j, y1>, <v_j, y2>}
-// of v = {q_0 .. q_k-1, y1, y2, r}.  q_k = y1 - sum_j b1_j q_j,
+// direction z_k+1 and stays), y2 = A y1, and beta[6j..] = {<v_j, y1>, <v_j, y2>,
+// <v_j, r>} of v = {q_0 .. q_k-1, y1, y2}.  q_k = y1 - sum_j b1_j q_j,
 // q_k+1 = y2 - sum_j b2_j q_j - g q_k, rout = rin - alpha1 q_k - alpha2 q_k+1;
-// with <q_j, r> = 0 and q_k orthogonal to the q_j
-//   <q_k, y2> = <y1, y2> - sum_j conj(b1_j) <q_j, y2>,   <q_k+1, r> = <y2, r> - conj(g) <q_k, r>.
+// with q_k orthogonal to the q_j
+//   <q_k, y2> = <y1, y2> - sum_j conj(b1_j) <q_j, y2>,
+//   <q_k, r> = <y1, r> - sum_j conj(b1_j) <q_j, r>,
+//   <q_k+1, r> = <y2, r> - sum_j conj(b2_j) <q_j, r> - conj(g) <q_k, r>.
+// r is orthogonal to the q_j only as far as it has not come down to rounding.
+// Taken for granted there, every further pair multiplied it: GCR(64) on a
+// spectrum of radius 0.5 about 1 ended at 2e-4 (FP32) and 2e-7 (FP64) of the
+// start instead of 8e-8 and 3e-15.
 // The span of {r, A r} is that of two steps (r after a step is r - alpha A r),
 // so a pair costs the basis two reads instead of four.  A y2 whose part outside
 // the basis is lost in rounding (1e-10 of its square) adds no direction.
@@ -233,42 +242,46 @@ __global__ void __launch_bounds__(kThreads) k_gcr_step_pair(VecList m, int k, co
   using P = Pack<T, W>;
   using V = typename P::V;
   __shared__ double2 c1[kVecs + kGroup], c2[kVecs + kGroup];
-  __shared__ double t1[kVecs], t2[kVecs], gr[kVecs], gi[kVecs];
+  // terms of the sums over the basis: ||q_k||^2, ||q_k+1||^2, <q_k, y2>, <q_k, r>, <q_k+1, r>
+  constexpr int kSums = 8;
+  __shared__ double term[kSums][kVecs + 1], sum[kSums];
   for (int j = threadIdx.x; j < k + kGroup; j += kThreads) {
     const double d = j < k ? q4[4 * j] : 0.0;
     double2 u = make_double2(0.0, 0.0), v = u;
-    double a = 0.0, b = 0.0, x = 0.0, z = 0.0;
+    double t[kSums];
+#pragma unroll
+    for (int i = 0; i < kSums; ++i) t[i] = 0.0;
     if (d > 0.0) {
-      const double* e = be + 4 * j;
+      const double* e = be + 6 * j;
       u = make_double2(e[0] / d, e[1] / d);
       v = make_double2(e[2] / d, e[3] / d);
-      a = (e[0] * e[0] + e[1] * e[1]) / d;
-      b = (e[2] * e[2] + e[3] * e[3]) / d;
-      x = u.x * e[2] + u.y * e[3];
-      z = u.x * e[3] - u.y * e[2];
+      t[0] = (e[0] * e[0] + e[1] * e[1]) / d;
+      t[1] = (e[2] * e[2] + e[3] * e[3]) / d;
+      t[2] = u.x * e[2] + u.y * e[3];
+      t[3] = u.x * e[3] - u.y * e[2];
+      t[4] = u.x * e[4] + u.y * e[5];
+      t[5] = u.x * e[5] - u.y * e[4];
+      t[6] = v.x * e[4] + v.y * e[5];
+      t[7] = v.x * e[5] - v.y * e[4];
     }
     c1[j] = u;
     c2[j] = v;
-    if (j < k) {
-      t1[j] = a;
-      t2[j] = b;
-      gr[j] = x;
-      gi[j] = z;
-    }
+    if (j < k)
+#pragma unroll
+      for (int i = 0; i < kSums; ++i) term[i][j] = t[i];
   }
   __syncthreads();
-  const double* e1 = be + 4 * k;  // <y1, y1>, <y1, y2>
-  const double* e2 = e1 + 4;      // <y2, y1>, <y2, y2>
-  const double* e3 = e2 + 4;      // <r, y1>, <r, y2>
-  double qq1 = e1[0], qq2 = e2[2];
-  cpx<double> g = mk(e1[2], e1[3]);
-  for (int j = 0; j < k; ++j) {
-    qq1 -= t1[j];
-    qq2 -= t2[j];
-    g.r -= gr[j];
-    g.i -= gi[j];
+  if (threadIdx.x < kSums) {
+    double t = 0.0;
+    for (int j = 0; j < k; ++j) t += term[threadIdx.x][j];
+    sum[threadIdx.x] = t;
   }
-  const cpx<double> r1 = mk(e3[0], -e3[1]);
+  __syncthreads();
+  const double* e1 = be + 6 * k;  // <y1, y1>, <y1, y2>, <y1, r>
+  const double* e2 = e1 + 6;      // <y2, y1>, <y2, y2>, <y2, r>
+  double qq1 = e1[0] - sum[0], qq2 = e2[2] - sum[1];
+  cpx<double> g = mk(e1[2] - sum[2], e1[3] - sum[3]);
+  const cpx<double> r1 = mk(e1[4] - sum[4], e1[5] - sum[5]);
   cpx<double> alpha1 = mk(0.0, 0.0), alpha2 = alpha1;
   if (qq1 > 0.0) {
     alpha1 = mk(r1.r / qq1, r1.i / qq1);
@@ -277,7 +290,7 @@ __global__ void __launch_bounds__(kThreads) k_gcr_step_pair(VecList m, int k, co
   } else {
     g = mk(0.0, 0.0);
   }
-  const cpx<double> r2 = mk(e3[2] - (g.r * r1.r + g.i * r1.i), -e3[3] - (g.r * r1.i - g.i * r1.r));
+  const cpx<double> r2 = mk(e2[4] - sum[6] - (g.r * r1.r + g.i * r1.i), e2[5] - sum[7] - (g.r * r1.i - g.i * r1.r));
   if (!(qq2 > 1e-10 * e2[2])) qq2 = 0.0;
   if (qq2 > 0.0) alpha2 = mk(r2.r / qq2, r2.i / qq2);
   if (blockIdx.x == 0) {
@@ -466,8 +479,8 @@ void blas_multi_cdot_b(int prec, const void* const* v, int k, const void* y, siz
     nc = std::min<size_t>(nc, std::max<size_t>(4096 / ((size_t)ng * nrhs), 8));
     nc = (nc + 7) / 8 * 8;
     const RedB oo{o.res + 2 * j0, o.rs, o.part, o.counter};
-    DISPATCH_W(prec, wide, k_multi_cdot, dim3((unsigned)(nc * ng), nrhs), m, kk, ng, (int)nc, y, nullptr, vs, n,
-               oo);
+    DISPATCH_W(prec, wide, k_multi_cdot, dim3((unsigned)(nc * ng), nrhs), m, kk, ng, (int)nc, y, nullptr, nullptr,
+               vs, n, oo);
   }
 }
 
@@ -476,23 +489,23 @@ void blas_multi_cdot(int prec, const void* const* v, int k, const void* y, size_
   blas_multi_cdot_b(prec, v, k, y, 0, n, 1, RedB{o.res, 0, o.partial, o.counter}, st);
 }
 
-void blas_multi_cdot_pair(int prec, const void* const* v, int k, const void* y1, const void* y2, size_t n,
-                          const RedOut& o, hipStream_t st) {
+void blas_multi_cdot_pair(int prec, const void* const* v, int k, const void* y1, const void* y2, const void* r,
+                          size_t n, const RedOut& o, hipStream_t st) {
   const int ng = (k + kGroup - 1) / kGroup;
   const VecList m = vec_list(v, k);
-  const bool wide = wide_ok(v, k, y1, y2, nullptr, 0, n, 1);
+  const bool wide = wide_ok(v, k, y1, y2, r, 0, n, 1);
   const size_t nv = packs(prec, wide, n);
-  // as blas_multi_cdot_b, with the partials of twice the values in the same space
+  // as blas_multi_cdot_b, with the partials of three times the values in the same space
   size_t nc = (std::min<size_t>((nv + kThreads - 1) / kThreads, kDotChunks) + 7) / 8 * 8;
-  nc = std::min<size_t>(nc, kRedPartials / (4 * kGroup) / ng / 8 * 8);
+  nc = std::min<size_t>(nc, kRedPartials / (6 * kGroup) / ng / 8 * 8);
   const RedB oo{o.res, 0, o.partial, o.counter};
   const dim3 grid((unsigned)(nc * ng)), block(kThreads);
-  if (prec == WCMG_F64)
-    hipLaunchKernelGGL((k_multi_cdot<double, 1, true>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, (size_t)0, n, oo);
-  else if (wide)
-    hipLaunchKernelGGL((k_multi_cdot<float, 2, true>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, (size_t)0, n, oo);
-  else
-    hipLaunchKernelGGL((k_multi_cdot<float, 1, true>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, (size_t)0, n, oo);
+#define WCMG_DP(T, W)                                                                                          \
+  hipLaunchKernelGGL((k_multi_cdot<T, W, 3>), grid, block, 0, st, m, k, ng, (int)nc, y1, y2, r, (size_t)0, n, oo)
+  if (prec == WCMG_F64) WCMG_DP(double, 1);
+  else if (wide) WCMG_DP(float, 2);
+  else WCMG_DP(float, 1);
+#undef WCMG_DP
   HIPCHK(hipGetLastError());
 }
 

@@ -200,10 +200,10 @@ struct RedB {
 void blas_norm2_b(int prec, const void* x, size_t vs, size_t n, int nrhs, const RedB& o, hipStream_t st);
 void blas_cdot_norm_b(int prec, const void* x, const void* y, size_t vs, size_t n, int nrhs, const RedB& o,
                       hipStream_t st);
-// two steps of an unpreconditioned GCR on one pass over its basis: beta[4j..] = {<v_j, y1>, <v_j, y2>},
-// then q_k, q_k+1 and the residual from them (v = {q_0 .. q_k-1, y1, y2, r}; y1 stays, y2 becomes q_k+1)
-void blas_multi_cdot_pair(int prec, const void* const* v, int k, const void* y1, const void* y2, size_t n,
-                          const RedOut& o, hipStream_t st);
+// two steps of an unpreconditioned GCR on one pass over its basis: beta[6j..] = {<v_j, y1>, <v_j, y2>, <v_j, r>},
+// then q_k, q_k+1 and the residual from them (v = {q_0 .. q_k-1, y1, y2}; y1 stays, y2 becomes q_k+1)
+void blas_multi_cdot_pair(int prec, const void* const* v, int k, const void* y1, const void* y2, const void* r,
+                          size_t n, const RedOut& o, hipStream_t st);
 void blas_gcr_step_pair(int prec, const void* const* q, int k, const void* y1, void* q1, void* y2, const void* rin,
                         void* rout, size_t n, const double* beta, double* qa, double* cj1, double* cj2,
                         hipStream_t st);

@@ -26,7 +26,7 @@ void GcrSpace::ensure(int restart) {
   // beta, qa, the orthogonalisation coefficients [slot][slot] (complex) and the
   // solution-update coefficients of a cycle
   if (!scal.p)
-    scal.alloc((4 * (kMaxRestart + 16) + 4 * kMaxRestart + 2 * kMaxRestart * kMaxRestart + 2 * kMaxRestart) *
+    scal.alloc((6 * (kMaxRestart + 16) + 4 * kMaxRestart + 2 * kMaxRestart * kMaxRestart + 2 * kMaxRestart) *
                sizeof(double));
 }
 
@@ -79,10 +79,10 @@ KrylovResult gcr(Ctx& c, GcrSpace& S, const OpFn& A, const OpFn* K, void* x, con
   // A z~_j is orthogonalised); cmat holds the orthogonalisation coefficients,
   // from which the solution update of a cycle is recovered
   double* beta = S.scal.as<double>();
-  double* qa = beta + 4 * (kMaxRestart + 16);
+  double* qa = beta + 6 * (kMaxRestart + 16);
   double* cmat = qa + 4 * kMaxRestart;
   double* ycoef = cmat + 2 * kMaxRestart * kMaxRestart;
-  std::vector<const void*> Qp(nf + restart), Zp(nf + restart), Dp(nf + restart + 3);
+  std::vector<const void*> Qp(nf + restart), Zp(nf + restart), Dp(nf + restart + 2);
   for (int j = 0; j < nf; ++j) {
     Qp[j] = defl->Q[j];
     Zp[j] = defl->Z[j];
@@ -130,9 +130,8 @@ KrylovResult gcr(Ctx& c, GcrSpace& S, const OpFn& A, const OpFn* K, void* x, con
     for (int j = 0; j < k; ++j) Dp[j] = Qp[j];
     Dp[k] = y1;
     Dp[k + 1] = y2;
-    Dp[k + 2] = z;
     double* cj = cmat + (size_t)2 * kMaxRestart * k;
-    blas_multi_cdot_pair(prec, Dp.data(), k + 3, y1, y2, n, R.out(beta), st);
+    blas_multi_cdot_pair(prec, Dp.data(), k + 2, y1, y2, z, n, R.out(beta), st);
     blas_gcr_step_pair(prec, Qp.data(), k, y1, S.Q[k].p, y2, z, rout, n, beta, qa, cj, cj + 2 * kMaxRestart, st);
     Qp[k] = S.Q[k].p;
     Qp[k + 1] = y2;
