@@ -233,8 +233,12 @@ __global__ void __launch_bounds__(kThreads) k_gcr_step(VecList m, int k, void* y
 // spectrum of radius 0.5 about 1 ended at 2e-4 (FP32) and 2e-7 (FP64) of the
 // start instead of 8e-8 and 3e-15.
 // The span of {r, A r} is that of two steps (r after a step is r - alpha A r),
-// so a pair costs the basis two reads instead of four.  A y2 whose part outside
-// the basis is lost in rounding (1e-10 of its square) adds no direction.
+// so a pair costs the basis two reads instead of four.  A y2 of whose square no
+// more than `lost` is outside the basis adds no direction: FP64 1e-14, a
+// hundred roundings of the difference that says so (1e-10 dropped directions
+// that eigenvalues in narrow clusters need: residuals of 2.3e-6 where 1.6e-6
+// was to be had); FP32 1e-10, above which a higher line did the same although
+// vectors stored in FP32 are orthogonal to 1e-7 only.
 template <typename T, int W>
 __global__ void __launch_bounds__(kThreads) k_gcr_step_pair(VecList m, int k, const void* y1, void* q1, void* y2,
                                                             const void* rin, void* rout, size_t n, const double* be,
@@ -291,7 +295,8 @@ __global__ void __launch_bounds__(kThreads) k_gcr_step_pair(VecList m, int k, co
     g = mk(0.0, 0.0);
   }
   const cpx<double> r2 = mk(e2[4] - sum[6] - (g.r * r1.r + g.i * r1.i), e2[5] - sum[7] - (g.r * r1.i - g.i * r1.r));
-  if (!(qq2 > 1e-10 * e2[2])) qq2 = 0.0;
+  constexpr double lost = sizeof(T) == 8 ? 1e-14 : 1e-10;
+  if (!(qq2 > lost * e2[2])) qq2 = 0.0;
   if (qq2 > 0.0) alpha2 = mk(r2.r / qq2, r2.i / qq2);
   if (blockIdx.x == 0) {
     if (threadIdx.x == 0) {
