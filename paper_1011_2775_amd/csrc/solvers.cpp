@@ -120,8 +120,9 @@ KrylovResult gcr(Ctx& c, GcrSpace& S, const OpFn& A, const OpFn* K, void* x, con
   // 16^3x32, is bound by reading its basis (24 vectors: dots and steps 204 ms
   // one by one, 102 ms in pairs).  The other user, the coarsest solve of a cycle
   // of fixed length outside the persistent kernel, is bound by its launches (of
-  // which a pair has six, two steps eight): 8^3x16 with 12 coarse steps, the
-  // outer iterations stay 19, a solve takes 8.1 ms in pairs and 11.9 before.
+  // which a pair has six, two steps eight): with 12 coarse steps a solve on
+  // 8^3x16 takes 7.8 ms in pairs and 9.9 without, on 16^3x32 21.4 and 23.8, in
+  // as many outer iterations (19, 23).
   auto enqueue_pair = [&](int k) {
     void* z = S.Z[k].p;
     void* y1 = S.Z[k + 1].p;
@@ -140,6 +141,22 @@ KrylovResult gcr(Ctx& c, GcrSpace& S, const OpFn& A, const OpFn* K, void* x, con
     Qp[k + 1] = y2;
     Zp[k] = z;
     Zp[k + 1] = y1;
+  };
+  // the last step of an odd length: a pair whose second direction is the first
+  // again and adds nothing, for the products with r; only its scalars are used
+  auto enqueue_last = [&](int k) {
+    void* z = S.Z[k].p;
+    void* y = S.Q[k].p;
+    if (k == 0) blas_copy(prec, z, r, n, st);
+    A(y, z);
+    for (int j = 0; j < k; ++j) Dp[j] = Qp[j];
+    Dp[k] = y;
+    Dp[k + 1] = y;
+    double* cj = cmat + (size_t)2 * kMaxRestart * k;
+    blas_multi_cdot_pair(prec, Dp.data(), k + 2, y, y, z, n, R.out(beta), st);
+    blas_gcr_step_pair(prec, Qp.data(), k, y, y, y, z, r, n, beta, qa, cj, cj + 2 * kMaxRestart, st);
+    Qp[k] = y;
+    Zp[k] = z;
   };
   const bool pairs = fixed && !K && nf == 0;
   // The top-level solve reads each step's scalars back asynchronously and,
@@ -162,6 +179,12 @@ KrylovResult gcr(Ctx& c, GcrSpace& S, const OpFn& A, const OpFn* K, void* x, con
         res.iters += 2;
         if (res.iters >= maxiter) break;
         continue;
+      }
+      if (pairs) {
+        enqueue_last(k);
+        ++k;
+        ++res.iters;
+        break;
       }
       if (!queued) {
         enqueue_step(k);

@@ -1,5 +1,5 @@
 """The paired steps of fixed-length GCR over long bases: three to nine groups of
-eight vectors, up to the longest basis, an odd last step, lengths far beyond
+eight vectors, up to the longest basis, odd lengths, lengths far beyond
 the point where the residual has come down to rounding, and the other user of
 the pairs, an unpreconditioned coarse solve of fixed length.
 
