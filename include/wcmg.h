@@ -280,7 +280,10 @@ int wcmg_apply_Ddag(void* ctx, int lat, int op, int prec, void* out, const void*
  * Level 0 fine vectors are canonical spinors (both parities); coarse
  * vectors of level l >= 1 are complex128 [Vc][2 Nv] in lexicographic
  * coarse-site order.  prec (F64/F32 on coarse levels) is the arithmetic.
- * Between level 0 and 1 the output may overlap the input (as in the applies). */
+ * Between level 0 and 1 the output may overlap the input (as in the applies).
+ * The first F16 transfer there makes a copy of the null vectors, rounded as it
+ * needs them (96 bytes a site and vector), which stays until they are rebuilt
+ * or the context ends. */
 int wcmg_restrict(void* ctx, int lat, int level, int prec, void* coarse_out, const void* fine_in, int nrhs);
 int wcmg_prolong(void* ctx, int lat, int level, int prec, void* fine_out, const void* coarse_in, int nrhs);
 
@@ -306,7 +309,9 @@ int wcmg_apply_coarse(void* ctx, int lat, int level, int op, int prec, void* out
  * when they fit; 3 and 4 give the same bits).  stats (optional):
  * iters, status, and
  * true_rel_res = ||b - Yhat x|| / ||b|| of the full coarse system in prec.
- * Requires a lattice with every coarse extent even (EDIM otherwise). */
+ * A work space of up to 32 MiB stays with the context for the next solve; a
+ * larger one is allocated for the call.  Requires a lattice with every coarse
+ * extent even (EDIM otherwise). */
 int wcmg_coarse_solve(void* ctx, int lat, int level, int prec, void* x, const void* b, double tol, int max_iter,
                       int restart, int launch, wcmg_stats* stats);
 

@@ -941,6 +941,9 @@ int wcmg_apply_coarse(void* ctx, int lat, int level, int op, int prec, void* out
   });
 }
 
+// work space of wcmg_coarse_solve that a context keeps from one call to the next
+constexpr size_t kCoarseSolveKept = kNoAllocScratchBytes;
+
 int wcmg_coarse_solve(void* ctx, int lat, int level, int prec, void* x, const void* b, double tol, int max_iter,
                       int restart, int launch, wcmg_stats* stats) {
   Ctx* c = as_ctx(ctx);
@@ -965,10 +968,14 @@ int wcmg_coarse_solve(void* ctx, int lat, int level, int prec, void* x, const vo
     if (launch != 1) {
       // one work space of the context, cleared by every call: allocating and
       // freeing it per call, with the separate clears, waits and norms that
-      // went with it, took 130 of 320 us at 512 sites x 48
+      // went with it, took 130 of 320 us at 512 sites x 48.  A larger one is
+      // given back at the end of the call
       const int grid = coarse_gcr_persistent_grid(prec, C.cg.n, C.cg.Vh);
       if (grid <= 0) fail(WCMG_ENODEV, "the device cannot run the persistent coarse solve");
-      void* base = c->scratch_buf(55, coarse_solve_noalloc_bytes(C, prec, std::min(restart, max_iter), grid));
+      const size_t need = coarse_solve_noalloc_bytes(C, prec, std::min(restart, max_iter), grid);
+      DBuf large;
+      if (need > kCoarseSolveKept) large.alloc(need);
+      void* base = large.p ? large.p : c->scratch_buf(55, need);
       coarse_solve_noalloc(*c, C, prec, base, grid, x, b, tol, max_iter, restart, launch == 2 || launch == 4,
                            launch >= 3, &s);
     } else {
