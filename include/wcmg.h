@@ -382,8 +382,9 @@ int wcmg_force(void* ctx, int lat, void* dU, const void* psi, const void* lam, i
  * result, so tuning never changes an answer.  Not during graph capture. */
 int wcmg_autotune(void* ctx, int on);
 /* The tuner's choices as text, one line per kernel variant
- * ("prec diag postinv Vh nrhs threads group microseconds"), written to buf
- * (NUL-terminated, truncated to len bytes). */
+ * ("prec diag postinv Vh nrhs threads group microseconds form Lx Ly Lz Lt";
+ * form: 1 for launches over both parities, plus 2 where the output is in the
+ * canonical layout), written to buf (NUL-terminated, truncated to len bytes). */
 int wcmg_autotune_report(void* ctx, char* buf, int len);
 
 /* The global sum behind every inner product of the Krylov solvers (the

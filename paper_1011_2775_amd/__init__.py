@@ -340,10 +340,11 @@ class Context:
         check(_lib.LIB.wcmg_autotune(self.h, int(bool(on))))
 
     def autotune_report(self):
-        """The tuned launch shapes: list of dicts (prec, diag, postinv, Vh, nrhs, threads, group, us)."""
+        """The tuned launch shapes: list of dicts (prec, diag, postinv, Vh, nrhs, threads, group, us, form,
+        Lx, Ly, Lz, Lt)."""
         buf = ctypes.create_string_buffer(1 << 16)
         check(_lib.LIB.wcmg_autotune_report(self.h, buf, len(buf)))
-        keys = ("prec", "diag", "postinv", "Vh", "nrhs", "threads", "group", "us")
+        keys = ("prec", "diag", "postinv", "Vh", "nrhs", "threads", "group", "us", "form", "Lx", "Ly", "Lz", "Lt")
         out = []
         for line in buf.value.decode().splitlines():
             vals = line.split()

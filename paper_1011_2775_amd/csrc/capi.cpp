@@ -1213,8 +1213,10 @@ int wcmg_autotune_report(void* ctx, char* buf, int len) {
     std::string out;
     for (const auto& kv : as_ctx(ctx)->tuner.best) {
       char line[160];
-      std::snprintf(line, sizeof(line), "%d %d %d %d %d %d %d %.3f\n", kv.first[0], kv.first[1], kv.first[2],
-                    kv.first[3], kv.first[4], kv.second.threads, kv.second.group, kv.second.us);
+      const auto& k = kv.first;
+      std::snprintf(line, sizeof(line), "%d %d %d %d %d %d %d %.3f %d %d %d %d %d\n", k[0], k[1], k[2],
+                    k[5] * k[6] * k[7] * k[8] / 2, k[3], kv.second.threads, kv.second.group, kv.second.us, k[4], k[5],
+                    k[6], k[7], k[8]);
       out += line;
     }
     std::snprintf(buf, (size_t)len, "%s", out.c_str());

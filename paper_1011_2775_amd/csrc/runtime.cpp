@@ -238,7 +238,8 @@ void FineOp::run_hop(DslashArgs& a, int diag, bool postinv) {
   if (ctx->tuner.on) {
     // launches over both parities and canonical outputs are variants of their own
     const int form = a.both + (a.canon_out ? 2 : 0);
-    const std::array<int, 6> key{prec * 3 + fp(), diag, postinv ? 1 : 0, F->g.Vh, nrhs, form};
+    const std::array<int, 9> key{prec * 3 + fp(), diag,     postinv ? 1 : 0, nrhs,    form,
+                                 a.g.L[0],        a.g.L[1], a.g.L[2],        a.g.L[3]};
     auto it = ctx->tuner.best.find(key);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     HIPCHK(hipStreamIsCapturing(st, &cs));

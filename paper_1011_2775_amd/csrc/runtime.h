@@ -34,15 +34,17 @@ struct KernelTimer {
 // ------------------------------------------------------------------ autotuner
 // Launch shape of the fine hop kernels (threads per block, right-hand sides
 // per thread), chosen by timing every candidate on the first launch of each
-// (precision, kernel variant, lattice, batch) and kept for the context.  All
-// candidates compute bitwise the same result.
+// (precision, kernel variant, lattice extents, batch, form) and kept for the
+// context.  All candidates compute bitwise the same result.
 struct Tuner {
   bool on = false;
   struct Choice {
     int threads, group;
     double us;
   };
-  std::map<std::array<int, 6>, Choice> best;
+  // precision pair, DIAG, clover inverse, right-hand sides, form (1 both parities, 2 canonical
+  // output), Lx, Ly, Lz, Lt: tiles of z and t make the extents matter, not the volume alone
+  std::map<std::array<int, 9>, Choice> best;
 };
 
 // ------------------------------------------------------------------ reductions
