@@ -241,9 +241,8 @@ int coarse_internal_index_host(const BlockGeom& bg, int lex);
 // storage vprec (F64, F32 or F16; F32 arithmetic for the last two).
 // canonical: fine vectors [V][4][3] and coarse vectors complex128, rounded to
 // the arithmetic on reading; else coarse vectors of the arithmetic's type, R
-// from fine vectors in the layout of vecs (one vector) and P to the
-// parity-split layout (even half at the pointer, odd half odd_bytes behind
-// it).  Parities p0 .. p0 + np - 1; up to kMaxTransfer vectors at once.
+// from fine vectors in the layout of vecs (one vector) and P to the even half
+// in the parity-split layout (one parity).  Parities p0 .. p0 + np - 1; up to kMaxTransfer vectors at once.
 constexpr int kMaxTransfer = 16;
 struct RestrictArgs {
   const void* vecs;
@@ -263,7 +262,6 @@ struct ProlongArgs {
   int nin;
   const void* in[kMaxTransfer];
   void* out[kMaxTransfer];
-  size_t odd_bytes;
   int p0, np;
   int internal_sites;
   DGeom g;

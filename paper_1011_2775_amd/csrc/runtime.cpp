@@ -143,10 +143,6 @@ const double* Reducer::fetch_rows_wait() {
   HIPCHK(hipEventSynchronize(ev2[0]));
   return host;
 }
-const double* Reducer::fetch_rows(const double* dev, size_t pitch, int width, int rows) {
-  fetch_rows_async(dev, pitch, width, rows);
-  return fetch_rows_wait();
-}
 // The copy is ordered after the reduction on the stream; values written by a
 // kernel straight into host-mapped memory were not reliably visible to the
 // host at stream synchronisation, so results always come back this way.
@@ -366,12 +362,6 @@ bool FineOp::Dr_red(void* out, void* y, const RedOut& o, void* e, const double* 
   if (ev) ctx->timer.end(id, ev);
   if (!ok) fail(WCMG_EINVAL, "fused smoother hop rejected after its checks passed");
   return true;
-}
-
-void FineOp::Mx(void* out, const void* x, int nrhs) {
-  w->ensure(prec, F->g, nrhs);
-  hop(w->t2.p, x, nullptr, 1, 0, true, 1.0, nrhs);  // w = A_oo^-1 H_oe x
-  hop(out, w->t2.p, x, 0, 2, false, -1.0, nrhs);    // out = A_ee x - H_eo w
 }
 
 void FineOp::Dr_dag(void* out, const void* y, int nrhs) {

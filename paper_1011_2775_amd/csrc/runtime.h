@@ -66,9 +66,8 @@ struct Reducer {
   // copy n results (from res, or from any device address) to the host and synchronise
   const double* fetch(int n) { return fetch_from(res, n); }
   const double* fetch_from(const double* dev, int n);
-  // rows doubles at dev + r * pitch (r < rows), `width` each, packed to host[r * width]
-  const double* fetch_rows(const double* dev, size_t pitch, int width, int rows);
-  // the same in two halves: work issued in between runs while the host waits for the copy
+  // rows doubles at dev + r * pitch (r < rows), `width` each, packed to host[r * width], in two
+  // halves: work issued in between runs while the host waits for the copy
   void fetch_rows_async(const double* dev, size_t pitch, int width, int rows);
   const double* fetch_rows_wait();
   // two-slot asynchronous form: the copy of n <= 8 doubles is ordered on the
@@ -134,9 +133,6 @@ struct FineOp {
   // D_r result) before D_r is applied to the updated y.
   bool Dr_red(void* out, void* y, const RedOut& o, void* e = nullptr, const double* coef = nullptr);
   void Dr_dag(void* out, const void* y, int nrhs = 1);
-  // the same reduced system in the variable x = A_ee^-1 y: out = A_ee x - H_eo A_oo^-1 H_oe x
-  // (two launches; its adjoint is gamma5 Mx gamma5)
-  void Mx(void* out, const void* x, int nrhs = 1);
   // full-lattice operators on (even, odd) halves
   void D(void* oe, void* oo, const void* ie, const void* io, int nrhs = 1);
   void Dp(void* oe, void* oo, const void* ie, const void* io, int nrhs = 1);

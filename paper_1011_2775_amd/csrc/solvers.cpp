@@ -1725,7 +1725,7 @@ static void build_deflation(Ctx& c, LatticeState& L, int li) {
   std::vector<double> qa(4 * (size_t)K, 0.0);
   for (int j = 0; j < K; ++j) qa[4 * j] = 1.0;
   L.defl_qa.alloc(qa.size() * sizeof(double));
-  L.defl_tmp.alloc((2 * (kMaxRestart + 16) + 4 * kMaxRestart) * sizeof(double));
+  L.defl_tmp.alloc(2 * kMaxRestart * sizeof(double));
   HIPCHK(hipMemcpyAsync(L.defl_qa.p, qa.data(), qa.size() * sizeof(double), hipMemcpyHostToDevice, st));
   HIPCHK(hipStreamSynchronize(st));
   L.defl_k = K;

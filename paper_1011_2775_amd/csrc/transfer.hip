@@ -141,7 +141,7 @@ struct FineIn<C, E, false> {
 };
 // The prolongation writes the canonical layout or the parity-split one of C.
 template <typename C, int E, bool CANON>
-__device__ __forceinline__ void store_fine(void* base, size_t odd_bytes, int Vh, int lex, int p, int s, int cu,
+__device__ __forceinline__ void store_fine(void* base, int Vh, int lex, int s, int cu,
                                            const cpx<C> v[E]) {
   if constexpr (CANON) {
     double2* q = reinterpret_cast<double2*>(base) + (size_t)lex * 12 + s * 6 + cu * E;
@@ -153,8 +153,7 @@ __device__ __forceinline__ void store_fine(void* base, size_t odd_bytes, int Vh,
       u = make_double2(v[0].r, v[0].i);
     else
       u = make_float4(v[0].r, v[0].i, v[1].r, v[1].i);
-    reinterpret_cast<typename VecUnit<C>::U*>(reinterpret_cast<char*>(base) + (p ? odd_bytes : 0))
-        [(size_t)(s * (6 / E) + cu) * Vh + (lex >> 1)] = u;
+    reinterpret_cast<typename VecUnit<C>::U*>(base)[(size_t)(s * (6 / E) + cu) * Vh + (lex >> 1)] = u;
   }
 }
 
@@ -545,7 +544,7 @@ __global__ void __launch_bounds__(256) k_prolong(ProlongArgs a) {
 #pragma unroll
     for (int n = 0; n < NT; ++n)
       if (n < a.nin)
-        store_fine<C, E, CANON>(a.out[n], a.odd_bytes, a.g.Vh, sites[ip * half + l], a.p0 + ip, s, cu, o[n]);
+        store_fine<C, E, CANON>(a.out[n], a.g.Vh, sites[ip * half + l], s, cu, o[n]);
   }
 }
 
@@ -916,6 +915,7 @@ void launch_restrict(int vprec, bool canonical, const RestrictArgs& a, hipStream
 void launch_prolong(int vprec, bool canonical, const ProlongArgs& a, hipStream_t st) {
   check_transfer(a.nvec, a.bg);
   if (a.nin < 1 || a.nin > kMaxTransfer) fail(WCMG_EINVAL, "prolongation of 1..16 vectors at once");
+  if (!canonical && a.np != 1) fail(WCMG_EINVAL, "prolongation of one parity to the parity-split layout");
   if (vprec == WCMG_F64) canonical ? prolong_t<double, true>(a, st) : prolong_t<double, false>(a, st);
   else if (vprec == WCMG_F32) canonical ? prolong_t<float, true>(a, st) : prolong_t<float, false>(a, st);
   else if (!canonical) prolong_t<__half, false>(a, st);
