@@ -85,6 +85,15 @@ def dr_compulsory_bytes(prec, nrhs=1):
     return fields / nrhs + spinors
 
 
+def apply_rates(prec, nrhs, canon, vh, ms):
+    """Rates of an apply of `ms` milliseconds: GBps of the compulsory bytes of D_r (the same whatever the launches
+    read twice or write beside), moved_GBps with what they move for the caller's canonical spinors (canon) too."""
+    comp = dr_compulsory_bytes(prec, nrhs)
+    rate = lambda b: b * nrhs * vh / (ms * 1e-3) / 1e9  # noqa: E731
+    return {"GBps": round(rate(comp), 1), "frac_of_8TBps": round(rate(comp) / PEAK_HBM_GBS, 3),
+            "moved_GBps": round(rate(comp + sum(canon)), 1)}
+
+
 def dslash_flops_per_site(diag, postinv):
     f = 1320  # 8 directions: projection, 2 SU(3) half-spinor products, reconstruction
     if postinv:
@@ -304,9 +313,10 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
     with the diagonal input fused) and D_r D_ee (two launches: hop with
     D_oo^-1 fused, hop with D_ee x fused), every launch of an apply timed with
     HIP events on the library stream; bandwidth from the compulsory bytes of
-    the reduced operator (dr_compulsory_bytes), which both forms share, plus
-    what the launches move for the caller's canonical spinors
-    (canonical_bytes).
+    the reduced operator (dr_compulsory_bytes), which both forms share, and
+    apart from it with what the launches move for the caller's canonical
+    spinors (canonical_bytes).  The launches read and write those themselves,
+    so the times contain what conversion launches beside them used to do.
     Protocol: 10 warm-up applies, then 5 trials of 40 applies (12 right-hand
     sides: 3 trials of 10), the median trial."""
     U = inputs.gauge_field_torch(dims, 0.5, 1003, device="cuda")
@@ -356,8 +366,7 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
                     trials.append((tot_ms, per, napply))
                 trials.sort(key=lambda t: t[0])
                 tot_ms, per, napply = trials[len(trials) // 2]
-                comp = (dr_compulsory_bytes(prec, nrhs) + sum(canon)) * nrhs * vh
-                gbps = comp / (tot_ms * 1e-3) / 1e9
+                rates = apply_rates(prec, nrhs, canon, vh, tot_ms)
                 kern = []
                 for kid, nm, nb in zip(ids, names, nbs):
                     n, ms = per[kid]
@@ -367,18 +376,17 @@ def dslash_headline(w, torch, inputs, dims=(24, 24, 24, 64), nrhs_list=(1, 12), 
                         kern.append({"kernel": nm, "launches_per_apply": n / napply, "avg_us": round(us, 2)})
                     else:
                         bl = nb * vh
-                        kern.append({"kernel": nm, "avg_us": round(us, 2), "bytes_per_launch": bl,
-                                     "GBps": round(bl / (us * 1e-6) / 1e9, 1),
+                        kern.append({"kernel": nm, "avg_us": round(us, 2), "moved_bytes_per_launch": bl,
+                                     "moved_GBps": round(bl / (us * 1e-6) / 1e9, 1),
                                      "traffic_bytes_per_launch": measured_traffic(nm) if dims == (24, 24, 24, 64)
                                      else None})
                 rec = {"form": "D_r, 3 launches" if op == w.OP_SCHUR else "D_r D_ee (variable x = D_ee^-1 y), "
                        "2 launches", "dr_us": round(tot_ms * 1e3, 2),
                        "compulsory_bytes_per_even_site_per_rhs": round(dr_compulsory_bytes(prec, nrhs), 1),
-                       "canonical_bytes_per_even_site_per_rhs": sum(canon),
-                       "GBps": round(gbps, 1), "frac_of_8TBps": round(gbps / PEAK_HBM_GBS, 3), "kernels": kern,
+                       "canonical_bytes_per_even_site_per_rhs": sum(canon), **rates, "kernels": kern,
                        "trials_us": [round(t[0] * 1e3, 2) for t in trials]}
                 if ceiling:
-                    rec["frac_of_copy"] = round(gbps / ceiling, 3)
+                    rec["frac_of_copy"] = round(rates["GBps"] / ceiling, 3)
                 out["%s%s_rhs%d" % (opname, name, nrhs)] = rec
         del v
     ctx.close()
@@ -894,7 +902,7 @@ def main():
     value = elapsed / steps_solves
     dr = None
     if headline:
-        dr = {k: {"GBps": v["GBps"], "frac_of_8TBps": v["frac_of_8TBps"], "frac_of_copy": v.get("frac_of_copy")}
+        dr = {k: {f: v.get(f) for f in ("dr_us", "GBps", "frac_of_8TBps", "frac_of_copy", "moved_GBps")}
               for k, v in headline.items()}
     line = {
         "metric": "time-to-solution @ rel.res 1e-10 (MG vs plain BiCGStab); Dslash GB/s",

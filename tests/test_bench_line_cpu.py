@@ -42,3 +42,14 @@ def test_line_without_optional_parts():
     short, details = bench.split_line(line)
     assert short["cpu_baseline"] is None and details["batched_24x24x24x64"] is None
     assert set(short) | set(details) == set(line)
+
+
+def test_rates_count_an_operand_once():
+    """The rate of an apply does not depend on what its launches read twice or write beside the result."""
+    vh = 24 ** 3 * 64 // 2
+    for prec, nrhs in ((0, 1), (2, 12)):
+        plain = bench.apply_rates(prec, nrhs, [0, 0], vh, 2.0)
+        moved = bench.apply_rates(prec, nrhs, bench.canonical_bytes(prec, "schur"), vh, 2.0)
+        assert plain["GBps"] == moved["GBps"] == round(bench.dr_compulsory_bytes(prec, nrhs) * nrhs * vh / 2e6, 1)
+        assert plain["moved_GBps"] == plain["GBps"] < moved["moved_GBps"]
+        assert moved["frac_of_8TBps"] == round(moved["GBps"] / bench.PEAK_HBM_GBS, 3)
