@@ -255,6 +255,7 @@ struct RestrictArgs {
   int internal_sites;  // coarse sites in internal order (else lexicographic)
   DGeom g;
   BlockGeom bg;
+  int col_groups = 1;  // set by the launcher: workgroups that share out the inputs of a batch
 };
 struct ProlongArgs {
   const void* vecs;

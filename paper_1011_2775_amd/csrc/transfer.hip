@@ -322,10 +322,11 @@ __global__ void __launch_bounds__(128) k_restrict(RestrictArgs a) {
 // are mostly padding (FP32 84 us against 117 us with two inputs).
 // FP64 sums: accumulated through the instructions, K / 4 roundings in a row,
 // they had an error of 9.3e-16 (blocks of 256 sites) where one vector had
-// 1.8e-16; the products of a step from zero, added to a sum of two words, have
-// 1.3e-16.  The second words take the registers of two wavefronts per SIMD with
-// two row and two column tiles, and the time stays (12 inputs, Nv 24: 291 and
-// 294 us).
+// 1.8e-16; the products of two steps from zero, added to a sum of two words,
+// have 1.6e-16 (of one step 1.3e-16, but a few blocks then wait for the adds: 75
+// us where 60 had been, now 65).  The second words take the registers of two
+// wavefronts per SIMD with two row and two column tiles, and the time stays (12
+// inputs, Nv 24: 291 and 292 us).
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <typename VT, bool CANON, int MT, int NT>
@@ -343,7 +344,9 @@ __global__ void __launch_bounds__(256, MT * NT <= (sizeof(VT) == 8 ? 2 : 4) ? 4 
   __syncthreads();
   // the wavefront's number in a scalar register: the loop's bounds are then scalar too
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), s = blockIdx.y;
-  const int q = lane >> 4, j = lane & 15, k0 = blockIdx.z * 16 * MT;
+  const int q = lane >> 4, j = lane & 15;
+  // row and column tiles of this workgroup, when they are shared out over several
+  const int zr = (int)gridDim.z / a.col_groups, k0 = ((int)blockIdx.z % zr) * 16 * MT, n0 = ((int)blockIdx.z / zr) * 8 * NT;
   const bool im = j & 1;
   const L* v[MT];
 #pragma unroll
@@ -352,7 +355,7 @@ __global__ void __launch_bounds__(256, MT * NT <= (sizeof(VT) == 8 ? 2 : 4) ? 4 
   const int pstep = a.bg.Vc * 2 * U / G;  // loads from one parity to the other
   const void* w[NT];
 #pragma unroll
-  for (int n = 0; n < NT; ++n) w[n] = fine_base<CANON, E>(a, a.in[min(8 * n + (j >> 1), a.nin - 1)], b, s);
+  for (int n = 0; n < NT; ++n) w[n] = fine_base<CANON, E>(a, a.in[min(n0 + 8 * n + (j >> 1), a.nin - 1)], b, s);
   d4 acc[MT][NT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
@@ -427,20 +430,16 @@ __global__ void __launch_bounds__(256, MT * NT <= (sizeof(VT) == 8 ? 2 : 4) ? 4 
       each(s2);
       i += 3;
     };
-    // FP64 results: the products of a step are summed from zero and added to a sum of two words
+    // FP64 results: the products of two steps are summed from zero and added to a sum of two words
     if constexpr (sizeof(VT) == 8) {
-      d4 low[MT][NT];
-#pragma unroll
-      for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int n = 0; n < NT; ++n) low[m][n] = (d4){0.0, 0.0, 0.0, 0.0};
-      auto exact_add = [&](const Step& st) {
-        d4 part[MT][NT];
+      d4 low[MT][NT], part[MT][NT];
+      auto clear = [&](d4 (&sum)[MT][NT]) {
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
-          for (int n = 0; n < NT; ++n) part[m][n] = (d4){0.0, 0.0, 0.0, 0.0};
-        multiply(st, part);
+          for (int n = 0; n < NT; ++n) sum[m][n] = (d4){0.0, 0.0, 0.0, 0.0};
+      };
+      auto exact_add = [&]() {
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -450,9 +449,36 @@ __global__ void __launch_bounds__(256, MT * NT <= (sizeof(VT) == 8 ? 2 : 4) ? 4 
             acc[m][n] = t;
           }
       };
-      while (i + 3 <= steps) three(exact_add);
-      if (i < steps) exact_add(s0);
-      if (i + 1 < steps) exact_add(s1);
+      clear(low);
+      while (i + 6 <= steps) {
+        clear(part);
+        load(at(i + 2), s2);
+        multiply(s0, part);
+        load(at(i + 3), s0);
+        multiply(s1, part);
+        exact_add();
+        clear(part);
+        load(at(i + 4), s1);
+        multiply(s2, part);
+        load(at(i + 5), s2);
+        multiply(s0, part);
+        exact_add();
+        clear(part);
+        load(at(i + 6), s0);
+        multiply(s1, part);
+        load(at(i + 7), s1);
+        multiply(s2, part);
+        exact_add();
+        i += 6;
+      }
+      auto one = [&](const Step& st) {
+        clear(part);
+        multiply(st, part);
+        exact_add();
+      };
+      while (i + 3 <= steps) three(one);
+      if (i < steps) one(s0);
+      if (i + 1 < steps) one(s1);
 #pragma unroll
       for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -476,7 +502,7 @@ __global__ void __launch_bounds__(256, MT * NT <= (sizeof(VT) == 8 ? 2 : 4) ? 4 
       __syncthreads();
       const int tid = threadIdx.x;
       const double sum = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
-      const int k = k0 + 16 * m + 4 * wave + q, rhs = 8 * n + (j >> 1);
+      const int k = k0 + 16 * m + 4 * wave + q, rhs = n0 + 8 * n + (j >> 1);
       if (k < a.nvec && rhs < a.nin) put_coarse<C, CANON>(a, rhs, b, s * a.nvec + k, j & 1, s ? -sum : sum);
       __syncthreads();
     }
@@ -864,15 +890,23 @@ void restrict_t(const RestrictArgs& a, hipStream_t st) {
     else                                                                                              \
       hipLaunchKernelGGL((k_restrict_mfma<VT, CANON, M, 2>), grid, dim3(256), shm, st, a);            \
   } while (0)
-  if (mt == 1) {
+  if (sizeof(VT) == 8 && a.nin > 8 && mt <= 2 && a.bg.Vc <= 64) {
+    // so few blocks that the column tiles find compute units of their own
+    RestrictArgs h = a;
+    h.col_groups = 2;
+    grid.z = 2;
+    if (mt == 1)
+      hipLaunchKernelGGL((k_restrict_mfma<VT, CANON, 1, 1>), grid, dim3(256), shm, st, h);
+    else
+      hipLaunchKernelGGL((k_restrict_mfma<VT, CANON, 2, 1>), grid, dim3(256), shm, st, h);
+  } else if (mt == 1) {
     WCMG_RM(1);
   } else if (mt == 2) {
     WCMG_RM(2);
   } else if (mt == 3) {
     WCMG_RM(3);
   } else if (sizeof(VT) == 8 && a.nin > 8) {
-    // four row tiles, two column tiles and their low words exceed the registers (1550 us at 16^4, blocks
-    // of 1024 sites, 12 inputs): two rows each
+    // four row tiles, two column tiles and their low words exceed the registers: two rows each
     grid.z = 2;
     WCMG_RM(2);
   } else {

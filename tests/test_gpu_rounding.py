@@ -6,7 +6,7 @@ roundings: short sums from zero, added in a tree or in two words.  Bounds on
 the relative error (Frobenius):
 
 * restriction of one vector and of batches (matrix instructions), with the
-  null vectors as prolongation gives them, blocks of 256 and 1024 sites: twelve
+  null vectors as prolongation gives them, blocks of 16 to 1024 sites: twelve
   roundings (the products of a lane's units, six to eight levels of sums), 2 u;
 * link force with and without its clover part: eight (the six sides of a link
   added one by one, the two halves of the hop), 1.63 u.
@@ -35,7 +35,8 @@ def split(v, dims, block):
 
 
 @pytest.mark.parametrize("dims,block,nvec", [((8, 8, 4, 8), (4, 4, 4, 4), 17), ((8, 8, 8, 8), (8, 8, 4, 4), 5),
-                                             ((4, 8, 8, 8), (4, 4, 4, 4), 33), ((8, 4, 4, 8), (4, 4, 4, 4), 64)])
+                                             ((4, 8, 8, 8), (4, 4, 4, 4), 33), ((8, 4, 4, 8), (4, 4, 4, 4), 64),
+                                             ((8, 8, 8, 4), (2, 2, 2, 2), 5), ((8, 8, 8, 4), (2, 2, 2, 2), 20)])
 def test_restriction(dims, block, nvec):
     rng = np.random.default_rng(11)
     cplx = lambda s: rng.standard_normal(s) + 1j * rng.standard_normal(s)  # noqa: E731
