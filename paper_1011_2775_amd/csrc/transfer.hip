@@ -881,6 +881,17 @@ void restrict_t(const RestrictArgs& a, hipStream_t st) {
     HIPCHK(hipGetLastError());
     return;
   }
+  if (sizeof(VT) < 8 && a.nin == 2 && a.bg.Vc < 256 && a.bg.bvol > 512) {
+    // few large blocks: two single launches have more workgroups than the tiles (64 blocks of 1024
+    // sites, Nv 20 / 40 / 64: 93 / 134 / 190 us, tiles 129 / 164 / 267; blocks of 256 and less lose)
+    RestrictArgs h = a;
+    h.nin = 1;
+    restrict_t<VT, CANON>(h, st);
+    h.in[0] = a.in[1];
+    h.out[0] = a.out[1];
+    restrict_t<VT, CANON>(h, st);
+    return;
+  }
   const int mt = transfer_tiles(a.nvec, 16);
   dim3 grid(xcd_grid(a.bg.Vc), 2);
 #define WCMG_RM(M)                                                                                    \
