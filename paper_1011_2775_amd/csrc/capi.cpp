@@ -812,10 +812,7 @@ static void transfer_fine(Ctx* c, LatticeState& L, int prec, int nrhs, void* out
   const size_t one = (size_t)g.V * 12 * 16, cone = (size_t)L.levels[0]->cg.V * L.levels[0]->cg.n * 16;
   const void* vecs = prec == WCMG_F64 ? T.v64.p : T.v32.p;
   const bool half = prec == WCMG_F16;
-  const size_t hb = spinor_bytes(WCMG_F16, g.Vh);
   in = apart(*c, in, nrhs * (to_coarse ? one : cone), out, nrhs * (to_coarse ? cone : one));
-  char* fe = nullptr;
-  char* fo = nullptr;
   char* rounded = nullptr;
   if (half) {
     if (!T.vh32.p) {
@@ -823,8 +820,6 @@ static void transfer_fine(Ctx* c, LatticeState& L, int prec, int nrhs, void* out
       launch_vec_half_rounded(T.vh32.p, T.v64.p, T.nvec, T.bg, c->st);
     }
     vecs = T.vh32.p;
-    fe = (char*)c->scratch_buf(42, hb);
-    fo = (char*)c->scratch_buf(43, hb);
     if (to_coarse) rounded = (char*)c->scratch_buf(46, one * std::min(nrhs, kMaxTransfer));
   }
   for (int r0 = 0; r0 < nrhs; r0 += kMaxTransfer) {
@@ -840,14 +835,10 @@ static void transfer_fine(Ctx* c, LatticeState& L, int prec, int nrhs, void* out
       a.g = dgeom(g);
       a.bg = T.bg;
       for (int i = 0; i < n; ++i) {
-        a.in[i] = (const char*)in + (size_t)(r0 + i) * one;
+        a.in[i] = half ? rounded + i * one : (const char*)in + (size_t)(r0 + i) * one;
         a.out[i] = (char*)out + (size_t)(r0 + i) * cone;
-        if (half) {
-          spinor_to_internal(WCMG_F16, fe, fo, a.in[i], g, false, c->st);
-          spinor_from_internal(WCMG_F16, rounded + i * one, fe, fo, g, false, c->st);
-          a.in[i] = rounded + i * one;
-        }
       }
+      if (half) spinor_round_half(rounded, (const char*)in + r0 * one, (size_t)n * g.V, c->st);
       launch_restrict(prec == WCMG_F64 ? WCMG_F64 : WCMG_F32, true, a, c->st);
     } else {
       ProlongArgs a{};
@@ -863,11 +854,7 @@ static void transfer_fine(Ctx* c, LatticeState& L, int prec, int nrhs, void* out
         a.out[i] = (char*)out + (size_t)(r0 + i) * one;
       }
       launch_prolong(prec == WCMG_F64 ? WCMG_F64 : WCMG_F32, true, a, c->st);
-      if (half)
-        for (int i = 0; i < n; ++i) {
-          spinor_to_internal(WCMG_F16, fe, fo, a.out[i], g, false, c->st);
-          spinor_from_internal(WCMG_F16, a.out[i], fe, fo, g, false, c->st);
-        }
+      if (half) spinor_round_half(a.out[0], a.out[0], (size_t)n * g.V, c->st);
     }
   }
   HIPCHK(hipStreamSynchronize(c->st));

@@ -100,6 +100,8 @@ void spinor_from_internal(int prec, void* canon, const void* even, const void* o
 // F32) and written as FP64; fields back to back, coefficients of right-hand side i at coef + i * cs
 void spinor_mr_last(int prec, void* dst64, const double* coef, size_t cs, const void* e, const void* r, int Vh,
                     int nrhs, hipStream_t st);
+// canonical complex128 spinors rounded to half-precision storage and back (out may be in)
+void spinor_round_half(void* out, const void* in, size_t sites, hipStream_t st);
 void spinor_convert(int prec_dst, void* dst, int prec_src, const void* src, int Vh, hipStream_t st);
 void spinor_gamma5(int prec, void* v, int Vh, hipStream_t st);
 
