@@ -211,11 +211,11 @@ __device__ __forceinline__ C3 madd(const C3& a, const C3& b) {
 // with products formed in place: the sum over both sides kept apart (four more
 // matrices alive) took 372 registers, one wavefront per SIMD and 316 us; loads
 // held behind what stands before them (fewer registers still) 390 us; 256
-// registers, two wavefronts, loads free within a square, 264 us.
+// registers, two wavefronts, loads free within a square, 251 us.
 // 48 products of 3x3 matrices a link (90 us of FP64 arithmetic at this size)
 // and the gather of 18 links and 24 Z of 72 bytes through L1 and L2 bound it.
 // 16^3x32, one pair of spinors: hop part 87 us and clover part 614 us as
-// launches of their own, 264 us now; the insertion 63 us, 29 us now.
+// launches of their own, 251 us now; the insertion 63 us, 27 us now.
 struct ForceLinks {
   const double2* gauge;
   const double* Z;

@@ -203,7 +203,7 @@ __device__ __forceinline__ const void* fine_base(const RestrictArgs& a, const vo
 // by halving (each exchange carries half of the values, 17 of them where a
 // butterfly per value takes 96), without LDS or barriers.  Bound by the read
 // of the vectors.  16^3x32, Nv 24: FP64, both parities, from the canonical layout
-// 435 -> 120 us (5.2 TB/s, a large copy's rate); FP32 even half with FP16 vectors
+// 435 -> 116 us (5.2 TB/s, a large copy's rate); FP32 even half with FP16 vectors
 // (the cycle) 35 -> 26 us.
 // FP64 sums: a lane's 24 units added in a row had an error of 2.7e-16 against
 // 1.8e-16 of a thread per site; three units at a time into a sum of two words
@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(128) k_restrict(RestrictArgs a) {
 // 240 us (from 9 to 16 inputs it grows by 13 us each, so the rows of 768 bytes
 // scattered over twelve fields bound it), the cycle's even half with FP16
 // vectors 400 -> 86 us; nine FP64 inputs in the block layout (a column of the
-// coarse build) 3830 -> 237 us.  One input stays on k_restrict: there the tiles
+// coarse build) 3830 -> 241 us.  One input stays on k_restrict: there the tiles
 // are mostly padding (FP32 84 us against 117 us with two inputs).
 // FP64 sums: accumulated through the instructions, K / 4 roundings in a row,
 // they had an error of 9.3e-16 (blocks of 256 sites) where one vector had
